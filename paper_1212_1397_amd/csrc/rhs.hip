@@ -1,4 +1,4 @@
-// F = h^2-scaled compact right-hand side, one thread per unknown node, for
+// F = h^2-scaled compact right-hand side for
 //  (a) a sum of Gaussian sources f = sum_s a_s exp(-|x - c_s|^2 / (2 sigma^2)),
 //  (b) a separable source f = sum_s c_s X_s(x) Y_s(y) Z_s(z) given by samples of
 //      each factor and its derivatives up to fourth order at the unknown nodes,
@@ -55,12 +55,14 @@ struct RhsArgs {
   double2 amp[kMaxSrc];
 };
 
-__device__ __forceinline__ void gauss_derivs(double x, double c, double is, double g[5]) {
+__device__ __forceinline__ void gauss_derivs(double x, double c, double is, double (&g)[5]) {
+#pragma clang fp contract(off)
   const double t = (x - c) * is;
   const double e = exp(-0.5 * t * t);
   const double t2 = t * t;
   const double he[5] = {1.0, t, t2 - 1.0, t * (t2 - 3.0), t2 * t2 - 6.0 * t2 + 3.0};
   double s = 1.0;
+#pragma unroll
   for (int k = 0; k < 5; ++k) {
     g[k] = s * he[k] * e;
     s *= -is;
@@ -72,115 +74,234 @@ __device__ __forceinline__ double2 cm(double2 a, double2 b) {
 }
 __device__ __forceinline__ double2 ca(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ double2 cs(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
+// factor arithmetic: real (Gaussians) or complex (separable tables)
+__device__ __forceinline__ double fm(double a, double b) { return a * b; }
+__device__ __forceinline__ double2 fm(double2 a, double2 b) { return cm(a, b); }
+__device__ __forceinline__ double fa(double a, double b) { return a + b; }
+__device__ __forceinline__ double2 fa(double2 a, double2 b) { return ca(a, b); }
+__device__ __forceinline__ double fs(double a, double s) { return a * s; }
+__device__ __forceinline__ double2 fs(double2 a, double s) { return cs(a, s); }
+__device__ __forceinline__ double2 cmf(double2 a, double b) { return cs(a, b); }
+__device__ __forceinline__ double2 cmf(double2 a, double2 b) { return cm(a, b); }
 
-// index of the derivative combinations accumulated per node
-enum {
-  D000, D200, D020, D002, D400, D040, D004, D220, D202, D022,
-  D100, D300, D120, D102, D010, D030, D210, D012, D001, D003, D201, D021, ND
+// One source is a product X(x) Y(y) Z(z).  Along a row of nodes (fixed y, z)
+// every term of F, face terms of the y and z faces included, is a row constant
+// times X, its second or its fourth derivative, so
+//   F(x) = sum_s C[0]_s X_s + C[1]_s (d2 X)_s + C[2]_s (d4 X)_s.
+// The constants of one source and row from the derivatives of Y and Z there;
+// qy, qz: node indices.
+template <typename S>
+__device__ __forceinline__ void row_coefs(const RhsCoef& a, const S (&gy)[5], const S (&gz)[5], int qy, int qz,
+                                          double2 (&C)[3]) {
+  const S p00 = fm(gy[0], gz[0]), p20 = fm(gy[2], gz[0]), p02 = fm(gy[0], gz[2]), p22 = fm(gy[2], gz[2]);
+  const S p40 = fm(gy[4], gz[0]), p04 = fm(gy[0], gz[4]), lap = fa(p20, p02);
+  // c_bil multiplies lap^2 f = quartic terms + 2 mixed ones, c_mix the mixed ones
+  const double2 mixc = ca(cs(a.c_bil, 2.0), a.c_mix);
+  C[0] = ca(ca(cmf(a.cK, p00), cmf(a.c_lap, lap)), ca(cmf(a.c_bil, fa(p40, p04)), cmf(mixc, p22)));
+  C[1] = ca(cmf(a.c_lap, p00), cmf(mixc, lap));
+  C[2] = cmf(a.c_bil, p00);
+#pragma unroll
+  for (int side = 0; side < 2; ++side) {
+    const double sg = side == 0 ? 1.0 : -1.0;
+    if (a.face[2 + side] == H6_NEUMANN && qy == (side == 0 ? 0 : a.n[1] + 1)) {
+      const S p10 = fm(gy[1], gz[0]), p30 = fm(gy[3], gz[0]), p12 = fm(gy[1], gz[2]);
+      C[0] = ca(C[0], cs(ca(ca(cmf(a.nN1, p10), cmf(a.nN3, p30)), cmf(a.nNm, p12)), sg));
+      C[1] = ca(C[1], cs(cmf(a.nNm, p10), sg));
+    }
+    if (a.face[4 + side] == H6_DIRICHLET || qz != (side == 0 ? 0 : a.n[2] + 1)) continue;
+    const S p01 = fm(gy[0], gz[1]), p03 = fm(gy[0], gz[3]), p21 = fm(gy[2], gz[1]);
+    if (a.face[4 + side] == H6_NEUMANN) {
+      C[0] = ca(C[0], cs(ca(ca(cmf(a.nN1, p01), cmf(a.nN3, p03)), cmf(a.nNm, p21)), sg));
+      C[1] = ca(C[1], cs(cmf(a.nNm, p01), sg));
+    } else {                                   // Sommerfeld: z'-derivatives f and its first three z' derivatives
+      const S f1 = fs(p01, sg), f3 = fs(p03, sg);
+      const double2 ik = a.ik, ik2 = cm(ik, ik), ik3 = cm(ik2, ik);
+      const double2 one = make_double2(1.0, 0.0);
+      const double2 fb1 = ca(cmf(ik, p00), cmf(one, f1));
+      const double2 fb2 = ca(ca(cmf(ik2, p00), cs(cmf(ik, f1), 2.0)), cmf(one, p02));
+      const double2 fb3 = ca(ca(cmf(ik3, p00), cs(cmf(ik2, f1), 3.0)), ca(cs(cmf(ik, p02), 3.0), cmf(one, f3)));
+      const double2 L0 = ca(cmf(ik, p20), cmf(one, fs(p21, sg)));      // Lbar: parts of X and of its second derivative
+      const double2 L2 = ca(cmf(ik, p00), cmf(one, f1));
+      const double2 F0 = ca(ca(cm(a.sA, fb1), cs(cm(a.sB, fb2), -1.0)), cm(a.sC, ca(fb3, cs(L0, -1.0))));
+      C[0] = ca(C[0], cm(a.e1mu3, ca(cs(F0, 2.0 * a.h), cm(a.mu1h5, L0))));
+      C[1] = ca(C[1], cm(a.e1mu3, ca(cs(cm(a.sC, L2), -2.0 * a.h), cm(a.mu1h5, L2))));
+    }
+  }
+}
+
+// Sources of the row kernel.  factor(s, axis, i, g): derivatives 0..4 of the
+// axis factor of source s at the i-th unknown; amp(s): its coefficient (zero
+// past the last source, whose factor is then source 0's).
+// coordinate of node q, rounded before the centre is subtracted (as everywhere
+// else; a fused multiply-add would shift every t by up to an ulp of the node)
+__device__ __forceinline__ double node_coord(int q, double h) {
+#pragma clang fp contract(off)
+  const double x = q * h;
+  return x;
+}
+
+struct GaussSrc {
+  using S = double;
+  const RhsArgs& a;
+  __device__ __forceinline__ int count() const { return a.nsrc; }
+  __device__ __forceinline__ void factor(int s, int axis, int i, double (&g)[5]) const {
+    const double* c = axis == 0 ? a.cx : axis == 1 ? a.cy : a.cz;
+    gauss_derivs(node_coord(i + a.c.qlo[axis], a.c.h), c[s < a.nsrc ? s : 0], a.inv_sigma, g);
+  }
+  __device__ __forceinline__ double2 amp(int s) const { return s < a.nsrc ? a.amp[s] : make_double2(0.0, 0.0); }
 };
 
-// F at node q from the accumulated derivative combinations d[] of f there
-__device__ double2 assemble(const RhsCoef& a, const double2 (&d)[ND], const int (&q)[3]) {
-  const double2 lap = ca(ca(d[D200], d[D020]), d[D002]);
-  const double2 mix = ca(ca(d[D220], d[D202]), d[D022]);
-  const double2 quart = ca(ca(d[D400], d[D040]), d[D004]);
-  // c_bil multiplies lap^2 f = quart + 2 mix; c_mix multiplies mix
-  double2 Fv = ca(ca(cm(a.cK, d[D000]), cm(a.c_lap, lap)),
-                  ca(cm(a.c_bil, ca(quart, cs(mix, 2.0))), cm(a.c_mix, mix)));
+// tab[a]: per term s and derivative order o the samples of the axis-a factor at
+// its unknown nodes, tab[a][(s * 5 + o) * dims[a] + i]
+struct TableSrc {
+  using S = double2;
+  const RhsCoef& c;
+  int nterms;
+  const double2* coef;
+  const double2* tab[3];
+  __device__ __forceinline__ int count() const { return nterms; }
+  __device__ __forceinline__ void factor(int s, int axis, int i, double2 (&g)[5]) const {
+    const double2* t = tab[axis] + size_t(s < nterms ? s : 0) * 5 * c.dims[axis] + i;
+#pragma unroll
+    for (int o = 0; o < 5; ++o) g[o] = t[size_t(o) * c.dims[axis]];
+  }
+  __device__ __forceinline__ double2 amp(int s) const { return s < nterms ? coef[s] : make_double2(0.0, 0.0); }
+};
 
-  // Neumann faces: normal derivative, its cube and the mixed terms
-  const int dn[3][4] = {{D100, D300, D120, D102}, {D010, D030, D210, D012}, {D001, D003, D201, D021}};
-  for (int ax = 0; ax < 3; ++ax)
-    for (int side = 0; side < 2; ++side) {
-      if (a.face[2 * ax + side] != H6_NEUMANN) continue;
-      const bool on = side == 0 ? q[ax] == 0 : q[ax] == a.n[ax] + 1;
-      if (!on) continue;
-      double2 RN = ca(ca(cm(a.nN1, d[dn[ax][0]]), cm(a.nN3, d[dn[ax][1]])),
-                      cm(a.nNm, ca(d[dn[ax][2]], d[dn[ax][3]])));
-      Fv = ca(Fv, cs(RN, side == 0 ? 1.0 : -1.0));
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// F as a matrix product on the FP64 matrix cores (v_mfma_f64_16x16x4): rows =
+// (re, im) of eight grid rows, columns = 16 nodes along x, k = four sources
+// (lane group g = lane / 16) times the orders 0, 2, 4.  Every lane computes the
+// row constants and the factors it feeds to the instruction itself, so a wave
+// needs no LDS: it holds the constants of 2 x 8 rows and 4 NQ sources and walks
+// along x.  Complex factors (tables) take a second product with the constants
+// times i.  Tile row 4 e + g is part e & 1 of grid row 2 g + (e >> 1), so a
+// lane ends with two whole complex values.  More than 4 NQ sources: the rest
+// is added by further passes over the wave's own rows.
+// The pass is bound by the store of F: 256 x 258 x 258, eight Gaussians, takes
+// 64 us (4.3 TB/s of stores), against 970 us with every node forming 22
+// derivative products per source from three exponentials.
+constexpr int kRhsTiles = 2, kRhsRows = 8 * kRhsTiles;      // grid rows per wave
+
+template <typename Src, int NQ>
+__device__ __forceinline__ void rhs_rows(const RhsCoef& a, const Src& src, double2* __restrict__ F) {
+  using S = typename Src::S;
+  constexpr bool kCplx = sizeof(S) == 16;
+  const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+  const int nx = a.dims[0], ny = a.dims[1], nrows = ny * a.dims[2];
+  const int row0 = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * kRhsRows;
+  if (row0 >= nrows) return;
+  // this lane's A rows: tile row c16 = part of grid row
+  const int sub = 2 * (c16 & 3) + (c16 >> 3), part = (c16 >> 2) & 1;
+  for (int s0 = 0; s0 == 0 || s0 < src.count(); s0 += 4 * NQ) {
+    double2 C[kRhsTiles][NQ][3];
+#pragma unroll
+    for (int t = 0; t < kRhsTiles; ++t) {
+      const int row = min(row0 + 8 * t + sub, nrows - 1);
+      const int j = row % ny, l = row / ny;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int sidx = s0 + 4 * q + g;
+        S gy[5], gz[5];
+        src.factor(sidx, 1, j, gy);
+        src.factor(sidx, 2, l, gz);
+        row_coefs<S>(a, gy, gz, j + a.qlo[1], l + a.qlo[2], C[t][q]);
+        const double2 am = src.amp(sidx);
+#pragma unroll
+        for (int o = 0; o < 3; ++o) {
+          const double2 v = cm(am, C[t][q][o]);
+          // A value of this lane's part against a real factor, and against an imaginary one
+          C[t][q][o] = make_double2(part ? v.y : v.x, part ? v.x : -v.y);
+        }
+      }
     }
-  // Sommerfeld z faces
-  for (int side = 0; side < 2; ++side) {
-    if (a.face[4 + side] != H6_SOMMERFELD) continue;
-    const bool on = side == 0 ? q[2] == 0 : q[2] == a.n[2] + 1;
-    if (!on) continue;
-    const double sg = side == 0 ? 1.0 : -1.0;
-    // z'-derivatives of f: f, f_z', f_z'z', f_z'z'z'
-    const double2 f0 = d[D000], f1 = cs(d[D001], sg), f2 = d[D002], f3 = cs(d[D003], sg);
-    const double2 ik = a.ik, ik2 = cm(ik, ik), ik3 = cm(ik2, ik);
-    const double2 fb1 = ca(cm(ik, f0), f1);
-    const double2 fb2 = ca(ca(cm(ik2, f0), cs(cm(ik, f1), 2.0)), f2);
-    const double2 fb3 = ca(ca(cm(ik3, f0), cs(cm(ik2, f1), 3.0)), ca(cs(cm(ik, f2), 3.0), f3));
-    const double2 Lb = ca(cm(ik, ca(d[D200], d[D020])), cs(ca(d[D201], d[D021]), sg));
-    const double2 Fb = ca(ca(cm(a.sA, fb1), cs(cm(a.sB, fb2), -1.0)),
-                          cm(a.sC, ca(fb3, cs(Lb, -1.0))));
-    Fv = ca(Fv, cm(a.e1mu3, ca(cs(Fb, 2.0 * a.h), cm(a.mu1h5, Lb))));
+    for (int x0 = 16 * blockIdx.y; x0 < nx; x0 += 16 * gridDim.y) {
+      const int x = x0 + c16, xc = min(x, nx - 1);
+      d4 acc[kRhsTiles];
+#pragma unroll
+      for (int t = 0; t < kRhsTiles; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        S gx[5];
+        src.factor(s0 + 4 * q + g, 0, xc, gx);
+#pragma unroll
+        for (int o = 0; o < 3; ++o)
+#pragma unroll
+          for (int t = 0; t < kRhsTiles; ++t) {
+            if constexpr (kCplx) {
+              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(C[t][q][o].x, gx[2 * o].x, acc[t], 0, 0, 0);
+              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(C[t][q][o].y, gx[2 * o].y, acc[t], 0, 0, 0);
+            } else {
+              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(C[t][q][o].x, gx[2 * o], acc[t], 0, 0, 0);
+            }
+          }
+      }
+      if (x < nx) {
+#pragma unroll
+        for (int t = 0; t < kRhsTiles; ++t)
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            const int row = row0 + 8 * t + 2 * g + p;
+            if (row >= nrows) continue;
+            double2* o = F + size_t(row) * nx + x;
+            double2 v = make_double2(acc[t][2 * p], acc[t][2 * p + 1]);
+            if (s0 > 0) v = ca(v, *o);
+            *o = v;
+          }
+      }
+    }
   }
-  return Fv;
 }
 
-// derivative orders (x, y, z) of each combination
-__constant__ int kOrd[ND][3] = {
-    {0, 0, 0}, {2, 0, 0}, {0, 2, 0}, {0, 0, 2}, {4, 0, 0}, {0, 4, 0}, {0, 0, 4}, {2, 2, 0},
-    {2, 0, 2}, {0, 2, 2}, {1, 0, 0}, {3, 0, 0}, {1, 2, 0}, {1, 0, 2}, {0, 1, 0}, {0, 3, 0},
-    {2, 1, 0}, {0, 1, 2}, {0, 0, 1}, {0, 0, 3}, {2, 0, 1}, {0, 2, 1}};
-
-__device__ __forceinline__ void node_of(const RhsCoef& a, size_t idx, int (&ijl)[3], int (&q)[3]) {
-  ijl[0] = int(idx % a.dims[0]);
-  ijl[1] = int((idx / a.dims[0]) % a.dims[1]);
-  ijl[2] = int(idx / (size_t(a.dims[0]) * a.dims[1]));
-  for (int ax = 0; ax < 3; ++ax) q[ax] = ijl[ax] + a.qlo[ax];
+// terms of the Neumann x faces, F +- R_N on the two planes of end nodes
+template <typename Src>
+__device__ __forceinline__ void rhs_xface(const RhsCoef& a, const Src& src, double2* __restrict__ F) {
+  using S = typename Src::S;
+  const int nx = a.dims[0], ny = a.dims[1], nrows = ny * a.dims[2];
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= 2 * nrows) return;
+  const int side = idx >= nrows, row = idx - side * nrows, i = side ? nx - 1 : 0;
+  double2 sum = make_double2(0.0, 0.0);
+  for (int s = 0; s < src.count(); ++s) {
+    S gx[5], gy[5], gz[5];
+    src.factor(s, 0, i, gx);
+    src.factor(s, 1, row % ny, gy);
+    src.factor(s, 2, row / ny, gz);
+    const S p00 = fm(gy[0], gz[0]), lap = fa(fm(gy[2], gz[0]), fm(gy[0], gz[2]));
+    const double2 r = ca(ca(cmf(a.nN1, fm(gx[1], p00)), cmf(a.nN3, fm(gx[3], p00))), cmf(a.nNm, fm(gx[1], lap)));
+    sum = ca(sum, cm(src.amp(s), r));
+  }
+  double2* o = F + size_t(row) * nx + i;
+  *o = ca(*o, cs(sum, side ? -1.0 : 1.0));
 }
 
+template <int NQ>
 __global__ __launch_bounds__(256) void rhs_kernel(RhsArgs a, double2* __restrict__ F) {
-  const size_t N = size_t(a.c.dims[0]) * a.c.dims[1] * a.c.dims[2];
-  const size_t idx = blockIdx.x * size_t(blockDim.x) + threadIdx.x;
-  if (idx >= N) return;
-  int ijl[3], q[3];
-  node_of(a.c, idx, ijl, q);
-  const double X = q[0] * a.c.h, Y = q[1] * a.c.h, Z = q[2] * a.c.h;
-  double2 d[ND];
-  for (int t = 0; t < ND; ++t) d[t] = make_double2(0.0, 0.0);
-  for (int s = 0; s < a.nsrc; ++s) {
-    double gx[5], gy[5], gz[5];
-    gauss_derivs(X, a.cx[s], a.inv_sigma, gx);
-    gauss_derivs(Y, a.cy[s], a.inv_sigma, gy);
-    gauss_derivs(Z, a.cz[s], a.inv_sigma, gz);
-    const double2 A = a.amp[s];
-    for (int t = 0; t < ND; ++t)
-      d[t] = ca(d[t], cs(A, gx[kOrd[t][0]] * gy[kOrd[t][1]] * gz[kOrd[t][2]]));
-  }
-  F[idx] = assemble(a.c, d, q);
+  const GaussSrc src{a};
+  rhs_rows<GaussSrc, NQ>(a.c, src, F);
+}
+__global__ __launch_bounds__(256) void rhs_xface_kernel(RhsArgs a, double2* __restrict__ F) {
+  const GaussSrc src{a};
+  rhs_xface(a.c, src, F);
 }
 
-// Separable source: tab[a] holds, per term s and derivative order o = 0..4,
-// the samples of the axis-a factor at the dims[a] unknown nodes of axis a:
-// tab[a][(s * 5 + o) * dims[a] + i].  coef[s] multiplies term s.
-__global__ __launch_bounds__(256) void rhs_separable_kernel(RhsCoef a, int nterms,
-                                                            const double2* __restrict__ coef,
+template <int NQ>
+__global__ __launch_bounds__(256) void rhs_separable_kernel(RhsCoef a, int nterms, const double2* __restrict__ coef,
                                                             const double2* __restrict__ tx,
                                                             const double2* __restrict__ ty,
-                                                            const double2* __restrict__ tz,
-                                                            double2* __restrict__ F) {
-  const size_t N = size_t(a.dims[0]) * a.dims[1] * a.dims[2];
-  const size_t idx = blockIdx.x * size_t(blockDim.x) + threadIdx.x;
-  if (idx >= N) return;
-  int ijl[3], q[3];
-  node_of(a, idx, ijl, q);
-  double2 d[ND];
-  for (int t = 0; t < ND; ++t) d[t] = make_double2(0.0, 0.0);
-  for (int s = 0; s < nterms; ++s) {
-    double2 gx[5], gy[5], gz[5];
-    for (int o = 0; o < 5; ++o) {
-      gx[o] = tx[size_t(s * 5 + o) * a.dims[0] + ijl[0]];
-      gy[o] = ty[size_t(s * 5 + o) * a.dims[1] + ijl[1]];
-      gz[o] = tz[size_t(s * 5 + o) * a.dims[2] + ijl[2]];
-    }
-    const double2 c = coef[s];
-    for (int t = 0; t < ND; ++t)
-      d[t] = ca(d[t], cm(c, cm(gx[kOrd[t][0]], cm(gy[kOrd[t][1]], gz[kOrd[t][2]]))));
-  }
-  F[idx] = assemble(a, d, q);
+                                                            const double2* __restrict__ tz, double2* __restrict__ F) {
+  const TableSrc src{a, nterms, coef, {tx, ty, tz}};
+  rhs_rows<TableSrc, NQ>(a, src, F);
+}
+__global__ __launch_bounds__(256) void rhs_separable_xface_kernel(RhsCoef a, int nterms,
+                                                                  const double2* __restrict__ coef,
+                                                                  const double2* __restrict__ tx,
+                                                                  const double2* __restrict__ ty,
+                                                                  const double2* __restrict__ tz,
+                                                                  double2* __restrict__ F) {
+  const TableSrc src{a, nterms, coef, {tx, ty, tz}};
+  rhs_xface(a, src, F);
 }
 
 // Dirichlet data g (n'x x n'y, x fastest) on a z face: Fp -= G g on the
@@ -265,6 +386,20 @@ RhsCoef rhs_coef(h6_plan P) {
   return a;
 }
 
+// launch shapes of the row kernels (four waves of kRhsRows rows) and of the x-face planes (Neumann x pair)
+struct RhsGrid {
+  dim3 rows;
+  unsigned xface;
+};
+RhsGrid rhs_grid(h6_plan P) {
+  const size_t nrows = size_t(P->dims[1]) * P->dims[2];
+  const unsigned wg = unsigned((nrows + 4 * kRhsRows - 1) / (4 * kRhsRows));
+  // small grids: the x tiles of a row group are shared out until there are
+  // about two waves per SIMD (each share forms the row constants again)
+  const unsigned tiles = unsigned(P->dims[0] + 15) / 16, split = (512 + wg - 1) / wg;
+  return RhsGrid{dim3(wg, split < tiles ? split : tiles), P->xmirror ? unsigned((2 * nrows + 255) / 256) : 0u};
+}
+
 // Neumann data on face plane (axis ax, side): beta = sum_s coef[s] T1_s(t1) T2_s(t2)
 // from tables tab1 / tab2 ([(s * 5 + o) * n_t + i], o = derivative order).
 struct NeumannFace {
@@ -317,8 +452,12 @@ hipError_t launch_rhs(h6_plan P, int nsrc, const double* centres, const double* 
   }
   hipEvent_t ev;
   timing_begin(P, KC_RHS, s, &ev);
-  const size_t nb = (P->N + 255) / 256;
-  hipLaunchKernelGGL(rhs_kernel, dim3(unsigned(nb)), dim3(256), 0, s, a, F);
+  const RhsGrid gr = rhs_grid(P);
+  if (nsrc <= 4)
+    hipLaunchKernelGGL(rhs_kernel<1>, gr.rows, dim3(256), 0, s, a, F);
+  else
+    hipLaunchKernelGGL(rhs_kernel<2>, gr.rows, dim3(256), 0, s, a, F);
+  if (gr.xface) hipLaunchKernelGGL(rhs_xface_kernel, dim3(gr.xface), dim3(256), 0, s, a, F);
   timing_end(P, KC_RHS, s, ev, double(P->N) * sizeof(double2));
   return hipGetLastError();
 }
@@ -351,9 +490,15 @@ hipError_t launch_rhs_separable(h6_plan P, int nterms, const double* coef, const
   if (e != hipSuccess) return e;
   hipEvent_t ev;
   timing_begin(P, KC_RHS, s, &ev);
-  const size_t nb = (P->N + 255) / 256;
-  hipLaunchKernelGGL(rhs_separable_kernel, dim3(unsigned(nb)), dim3(256), 0, s, rhs_coef(P), nterms,
-                     dcoef, dtab[0], dtab[1], dtab[2], F);
+  const RhsGrid gr = rhs_grid(P);
+  const RhsCoef a = rhs_coef(P);
+  if (nterms <= 4)
+    hipLaunchKernelGGL(rhs_separable_kernel<1>, gr.rows, dim3(256), 0, s, a, nterms, dcoef, dtab[0], dtab[1], dtab[2], F);
+  else
+    hipLaunchKernelGGL(rhs_separable_kernel<2>, gr.rows, dim3(256), 0, s, a, nterms, dcoef, dtab[0], dtab[1], dtab[2], F);
+  if (gr.xface)
+    hipLaunchKernelGGL(rhs_separable_xface_kernel, dim3(gr.xface), dim3(256), 0, s, a, nterms, dcoef, dtab[0], dtab[1],
+                       dtab[2], F);
   timing_end(P, KC_RHS, s, ev, double(P->N) * sizeof(double2));
   e = hipGetLastError();
   if (e != hipSuccess) return e;
