@@ -285,6 +285,44 @@ hipError_t build_bluestein(AxisXform& ax, hipStream_t s) {
   return e;
 }
 
+// Tables of the power-of-two FFT path (xform_fft.hip): twiddles exp(-2 pi i t / M)
+// and sin / cos(pi q / M), in double and in single precision, in one device
+// allocation.
+hipError_t build_fft(AxisXform& ax, hipStream_t s) {
+  const int M = ax.M;
+  const size_t D = size_t(M) * sizeof(double2), bytes = 2 * D + D / 2 + D / 2;   // tw, sin + cos, tw_f, sin_f + cos_f
+  std::vector<char> host(bytes);
+  double2* tw = reinterpret_cast<double2*>(host.data());
+  double* sq = reinterpret_cast<double*>(host.data() + D);
+  double* cq = sq + M;
+  float2* twf = reinterpret_cast<float2*>(host.data() + 2 * D);
+  float* sf = reinterpret_cast<float*>(host.data() + 2 * D + D / 2);
+  float* cf = sf + M;
+  for (int t = 0; t < M; ++t) {
+    const long double ang = -2.0L * M_PIl * (long double)t / M, half = M_PIl * (long double)t / M;
+    tw[t] = make_double2(double(cosl(ang)), double(sinl(ang)));
+    sq[t] = double(sinl(half));
+    cq[t] = double(cosl(half));
+    twf[t] = make_float2(float(tw[t].x), float(tw[t].y));
+    sf[t] = float(sq[t]);
+    cf[t] = float(cq[t]);
+  }
+  char* mem = nullptr;
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&mem), bytes);
+  if (e != hipSuccess) return e;
+  ax.fft_mem = mem;
+  FftTables& t = ax.fft;
+  t.M = M;
+  t.tw = reinterpret_cast<const double2*>(mem);
+  t.sin_q = reinterpret_cast<const double*>(mem + D);
+  t.cos_q = t.sin_q + M;
+  t.tw_f = reinterpret_cast<const float2*>(mem + 2 * D);
+  t.sin_f = reinterpret_cast<const float*>(mem + 2 * D + D / 2);
+  t.cos_f = t.sin_f + M;
+  e = hipMemcpyAsync(mem, host.data(), bytes, hipMemcpyHostToDevice, s);
+  return e == hipSuccess ? hipStreamSynchronize(s) : e;
+}
+
 // Tables of the Rader path for a prime M with M - 1 = 256 (xform_rader.hip).
 hipError_t build_rader(AxisXform& ax, hipStream_t s) {
   const int M = ax.M, P1 = M - 1;
@@ -382,6 +420,7 @@ void free_plan(h6_plan P) {
   if (P->ev_order) (void)hipEventDestroy(P->ev_order);
   for (auto& a : P->ax) (void)hipFree(a.rader_mem);
   for (auto& a : P->ax) (void)hipFree(a.blue_mem);
+  for (auto& a : P->ax) (void)hipFree(a.fft_mem);
   (void)hipFree(P->d_stencil);
   (void)hipFree(P->d_lambda_x);
   (void)hipFree(P->d_lambda_y);
@@ -529,6 +568,10 @@ h6_status setup_impl(const h6_params* p, hipStream_t s, h6_plan* out, std::strin
       const int M = P->ax[a].M;
       if (e == hipSuccess && 16 * (2 * M - 2) >= 15 * bluestein_length(M)) P->ax[a].fast = 2;
     }
+    else if (fft_ok(P->ax[a].M) && !std::getenv("H6_DENSE_TRANSFORMS")) {
+      e = build_fft(P->ax[a], s);
+      if (e == hipSuccess) P->ax[a].fast = 3;
+    }
     P->ax[a].lines = a == 0 ? 4 : 16;     // untuned default: best on gfx950 at 256^3
   }
   const size_t elem = p->precision == H6_MIXED ? sizeof(float2) : sizeof(double2);
@@ -647,10 +690,11 @@ h6_status autotune(h6_plan P, const char* cache_path, hipStream_t s) {
   std::snprintf(key, sizeof key, "h6tune3 %s %d %d %d %d", devname, P->dims[0], P->dims[1], P->dims[2],
                 P->p.precision);
   const bool can_x = P->ax[0].rader_mem != nullptr, can_y = P->ax[1].rader_mem != nullptr;
-  // transform variant code of the cache (0 dense, 1 Rader, 2 Bluestein) -> the variants this plan has
+  // transform variant code of the cache (0 dense, 1 Rader, 2 Bluestein, 3 power-of-two FFT) -> the variants this plan has
   auto fast_code = [&](int ax, int code) {
     if (code == 1 && P->ax[ax].rader_mem) return 1;
     if (code == 2 && P->ax[ax].blue_mem) return 2;
+    if (code == 3 && P->ax[ax].fft_mem) return 3;
     return 0;
   };
   if (cache_path) {
@@ -733,14 +777,15 @@ h6_status autotune(h6_plan P, const char* cache_path, hipStream_t s) {
     P->ax[ax].fast = best_lines ? 1 : 0;
     P->ax[ax].lines = best_lines ? best_lines : (ax == 0 ? 4 : 16);
   }
-  // the Bluestein path against the dense product (odd M <= 255)
+  // the Bluestein path (odd M <= 255) or the power-of-two FFT against the dense product
   for (int ax = 0; ax < 2; ++ax) {
-    if (!P->ax[ax].blue_mem) continue;
+    const int fft = P->ax[ax].blue_mem ? 2 : P->ax[ax].fft_mem ? 3 : 0;
+    if (!fft) continue;
     P->ax[ax].fast = 0;
     const double dense = time_it([&] { (void)launch_pinv(P, x, y, s); });
-    P->ax[ax].fast = 2;
-    const double blue = time_it([&] { (void)launch_pinv(P, x, y, s); });
-    P->ax[ax].fast = blue <= dense ? 2 : 0;
+    P->ax[ax].fast = fft;
+    const double t = time_it([&] { (void)launch_pinv(P, x, y, s); });
+    P->ax[ax].fast = t <= dense ? fft : 0;
   }
   P->timing.enabled = timing;
   const hipError_t err = hipStreamSynchronize(s);

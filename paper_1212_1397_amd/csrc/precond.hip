@@ -9,9 +9,9 @@
 // W_qm = cos(pi q m / M) (q, m = 0..M); W^{-1} = (2/M) W^T and
 // (2/M) C W^T C (C = diag(1/2, 1, .., 1, 1/2)) respectively.
 //
-// Steps 1, 2, 4, 5 use the Rader FFT path for M = 257 (xform_rader.hip) and
-// the dense basis-matrix products on the matrix cores otherwise
-// (xform_dense.hip).  Compute type R is double (FP64 plans) or float (mixed
+// Steps 1, 2, 4, 5 use an FFT path for M = 257 (xform_rader.hip), M = 64 .. 512
+// a power of two (xform_fft.hip) and some odd M (xform_bluestein.hip), and the
+// dense basis-matrix products on the matrix cores otherwise (xform_dense.hip).  Compute type R is double (FP64 plans) or float (mixed
 // plans, complex64 intermediates); the input r and output z are complex128 in
 // both.
 #include <mutex>
@@ -239,6 +239,8 @@ hipError_t pinv_impl(h6_plan P, const Tin* r, Tout* z, hipStream_t s, int part, 
                              P->skip));
     else if (X.fast == 2)
       note(launch_bluestein_x<R>(X.neumann, inv, src, dst, nlines_x, X.L, X.blue, s, accumulate, P->skip));
+    else if (X.fast == 3)
+      note(launch_fft_x<R>(X.neumann, inv, src, dst, nlines_x, X.L, X.fft, s, accumulate, P->skip));
     else
       note(launch_dense_x<R>(X, inv, src, dst, nlines_x, accumulate, s, P->skip));
     timing_end(P, KC_XFORM_X, s, ev, Nd * (sizeof(*src) + sizeof(*dst) * (accumulate ? 2 : 1)));
@@ -249,6 +251,8 @@ hipError_t pinv_impl(h6_plan P, const Tin* r, Tout* z, hipStream_t s, int part, 
       note(launch_rader_y<R>(Y.neumann, inv, src, dst, nx, Y.L, nz, Y.rader, s, Y.lines, P->skip));
     else if (Y.fast == 2)
       note(launch_bluestein_y<R>(Y.neumann, inv, src, dst, nx, Y.L, nz, Y.blue, s, P->skip));
+    else if (Y.fast == 3)
+      note(launch_fft_y<R>(Y.neumann, inv, src, dst, nx, Y.L, nz, Y.fft, s, P->skip));
     else
       note(launch_dense_y<R>(Y, inv, src, dst, nx, nz, s, P->skip));
     timing_end(P, KC_XFORM_Y, s, ev, Nd * 2 * sizeof(T2));

@@ -772,7 +772,8 @@ h6_status queue_create(h6_plan* plans, int count, int m, int lanes, h6_queue* ou
       ln.P->stencil_tz = src->stencil_tz;
       for (int a = 0; a < 2; ++a) {
         const int f = src->ax[a].fast;
-        if (f == 0 || (f == 1 && ln.P->ax[a].rader_mem) || (f == 2 && ln.P->ax[a].blue_mem)) {
+        if (f == 0 || (f == 1 && ln.P->ax[a].rader_mem) || (f == 2 && ln.P->ax[a].blue_mem) ||
+            (f == 3 && ln.P->ax[a].fft_mem)) {
           ln.P->ax[a].fast = f;
           ln.P->ax[a].lines = src->ax[a].lines;
         }
