@@ -270,7 +270,7 @@ h6_status helmholtz6_solve_batch_queue(h6_plan* plans, const void* const* F, voi
 h6_status helmholtz6_set_graphs(h6_plan plan, int enable);
 
 /* Autotuner: times the variants of the plan's kernels on the plan's own grid
- * (stencil z-chunk depth 8, 16 or 32 planes per workgroup; for n'x or n'y + 1
+ * (stencil z-chunk depth 2 to 32 planes per workgroup; for n'x or n'y + 1
  * = 257 also the dense transform against the Rader transform at 4 or 8 lines
  * per workgroup along x and 8 or 16 columns along y; for an odd n + 1 up to
  * 255 the dense transform against the Bluestein (chirp-z) transform, for

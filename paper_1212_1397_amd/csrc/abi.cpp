@@ -496,6 +496,7 @@ h6_status setup_impl(const h6_params* p, hipStream_t s, h6_plan* out, std::strin
   P->k = cplx(p->k_re, p->k_im);
   P->kappa = (P->k * p->h) * (P->k * p->h);
   build_stencil(P);
+  stencil_defaults(P);
   for (int a = 0; a < 2; ++a) {
     P->ax[a].L = P->dims[a];
     P->ax[a].M = p->n[a] + 1;
@@ -706,7 +707,7 @@ h6_status autotune(h6_plan P, const char* cache_path, hipStream_t s) {
         if (std::strncmp(line, key, kl) == 0 && line[kl] == ' ' &&
             std::sscanf(line + kl, " tz=%d xfast=%d yfast=%d xlines=%d ylines=%d", &tz, &xf, &yf, &xl,
                         &yl) == 5 &&
-            (tz == 8 || tz == 16 || tz == 32) && rader_lines_ok(0, xl) && rader_lines_ok(1, yl)) {
+            stencil_tz_ok(tz) && rader_lines_ok(0, xl) && rader_lines_ok(1, yl)) {
           std::fclose(f);
           P->stencil_tz = tz;
           P->ax[0].fast = fast_code(0, xf);
@@ -754,7 +755,7 @@ h6_status autotune(h6_plan P, const char* cache_path, hipStream_t s) {
   double2* y = static_cast<double2*>(b);
   int best_tz = 16;
   double best_ms = 1e30;
-  for (int tz : {8, 16, 32}) {
+  for (int tz : {2, 4, 8, 16, 32}) {
     P->stencil_tz = tz;
     const double ms = time_it([&] { (void)launch_stencil(P, x, y, nullptr, nullptr, nullptr, s); });
     if (ms < best_ms) { best_ms = ms; best_tz = tz; }

@@ -154,7 +154,8 @@ struct h6_plan_s {
   std::vector<hipGraphExec_t> step_graphs;     // one per step index (mode 1)
   hipGraphExec_t cycle_graph = nullptr;        // one restart cycle (mode 2)
   h6::GraphKey graph_key;
-  int stencil_tz = 16;                         // autotuned stencil z-chunk (8, 16 or 32)
+  int stencil_tx = 64;                         // stencil tile width (64 x 8 or 32 x 16)
+  int stencil_tz = 16;                         // stencil z-chunk (2 .. 32 planes; may be autotuned)
   bool spec_done = false;                      // exact spectrum bounds of A A_p^{-1} (Dirichlet)
   h6_status spec_status = H6_OK;
   double spec_lo = 0.0, spec_hi = 0.0;
@@ -223,6 +224,9 @@ hipError_t launch_stencil_f32in(h6_plan P, const float2* x, double2* y, hipStrea
 // callers that only hand r to a complex64 preconditioner
 // workgroups of a stencil launch on this plan (one residual-norm partial each)
 int stencil_workgroups(h6_plan P);
+// tile width and z-chunk depth of an untuned plan
+void stencil_defaults(h6_plan P);
+bool stencil_tz_ok(int tz);
 hipError_t launch_resid_f32out(h6_plan P, const double2* U, float2* r, const double2* F,
                                double* partials, int* nparts, hipStream_t s, double* fpartials = nullptr);
 // Dense (matrix-core) transforms along x / y with the axis' basis matrices

@@ -8,23 +8,22 @@
 // and D_x D_y).  Neumann x/y faces enter through mirror ghosts, Dirichlet
 // faces through zeros.
 //
-// Launch shape (2.5D march): a workgroup of 256 threads owns a 64 x 8 x-y tile
-// and a chunk of up to kTZ z-planes (8, 16 or 32: the plan's autotuned depth).  It streams the planes of its chunk plus
-// one halo plane on each side through a double-buffered LDS tile of 66 x 10
-// complex values, computes S_p once per plane, and scatters it into the two
+// Launch shape (2.5D march): a workgroup of 256 threads owns a 64 x 8 or 32 x 16
+// x-y tile and a chunk of up to kTZ z-planes (2 .. 32; stencil_defaults, or the
+// autotuner's depth).  It streams the planes of its chunk plus one halo plane on
+// each side through a double-buffered LDS tile with a one-point halo, computes S_p once per plane, and scatters it into the two
 // running row accumulators.  Each plane is read from HBM once per tile
 // (halo columns and the two halo planes are the only re-reads).  Workgroup
 // ids are remapped so that consecutive tiles land on the same XCD (shared L2
 // for halos).
+#include <type_traits>
+
 #include "h6_internal.h"
 
 namespace h6 {
 namespace {
 
-constexpr int kTX = 64, kTY = 8;      // x-y tile; the z chunk (8, 16 or 32 planes) is a template parameter
-constexpr int kLX = kTX + 2, kLY = kTY + 2;
 constexpr int kThreads = 256;
-constexpr int kLoads = (kLX * kLY + kThreads - 1) / kThreads;   // 3
 
 struct S3 {
   double2 c, e, k;
@@ -45,13 +44,15 @@ __device__ __forceinline__ void apply_w(double2& acc, const W9& w, const S3& s) 
 
 __device__ __forceinline__ double2 add2(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 
-template <bool RESID, typename Tin, typename Tout, int kTZ>
+template <bool RESID, typename Tin, typename Tout, int kTX, int kTZ>
 __global__ __launch_bounds__(kThreads) void stencil_kernel(
     const Tin* __restrict__ x, Tout* __restrict__ y, const double2* __restrict__ F,
     double* __restrict__ partials, double* __restrict__ fpartials, const StencilTable* __restrict__ W,
     int nx, int ny, int nz,
     int xmir, int ymir, int zlo_cl, int zhi_cl, int ntx, int nty, int nwg, const int* __restrict__ skip) {
   if (skip && *skip) return;
+  constexpr int kTY = 512 / kTX, kLX = kTX + 2, kLY = kTY + 2, kRows = kThreads / kTX;
+  constexpr int kLoads = (kLX * kLY + kThreads - 1) / kThreads;   // 3
   __shared__ double2 tile[2][kLY][kLX];
   __shared__ double red[kThreads / 64];
 
@@ -62,7 +63,7 @@ __global__ __launch_bounds__(kThreads) void stencil_kernel(
   const int x0 = tx_i * kTX, y0 = ty_i * kTY, z0 = tz_i * kTZ;
   const int z1 = min(z0 + kTZ, nz);
   const int tid = threadIdx.x;
-  const int tx = tid & 63, ty = tid >> 6;
+  const int tx = tid % kTX, ty = tid / kTX;
   const size_t plane = size_t(nx) * ny;
 
   // element e of the (kLY x kLX) tile -> global (gx, gy) with ghost rules;
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(kThreads) void stencil_kernel(
     const W9 w_next = W->w[row_type(p + 1)][0];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const int r = ty + 4 * s + 1, c = tx + 1;
+      const int r = ty + kRows * s + 1, c = tx + 1;
       S3 S;
       S.c = tile[b][r][c];
       S.e = add2(add2(tile[b][r][c - 1], tile[b][r][c + 1]), add2(tile[b][r - 1][c], tile[b][r + 1][c]));
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(kThreads) void stencil_kernel(
       // row p-1 receives its +1 plane and is complete
       if (p - 1 >= z0) {
         apply_w(acc_a[s], w_prev, S);
-        const int gx = x0 + tx, gy = y0 + ty + 4 * s;
+        const int gx = x0 + tx, gy = y0 + ty + kRows * s;
         if (gx < nx && gy < ny) {
           const size_t o = size_t(p - 1) * plane + gx + size_t(nx) * gy;
           double2 out = acc_a[s];
@@ -209,10 +210,11 @@ __global__ __launch_bounds__(kThreads) void stencil_kernel(
 
 }  // namespace
 
-template <typename Tin, typename Tout, int kTZ>
+template <typename Tin, typename Tout, int kTX, int kTZ>
 hipError_t stencil_launch(h6_plan P, const Tin* x, Tout* y, const double2* F, double* partials,
                           int* nparts, hipStream_t s, double* fpartials) {
   const int nx = P->dims[0], ny = P->dims[1], nz = P->dims[2];
+  constexpr int kTY = 512 / kTX;
   const int ntx = (nx + kTX - 1) / kTX, nty = (ny + kTY - 1) / kTY, ntz = (nz + kTZ - 1) / kTZ;
   const int nwg = ntx * nty * ntz;
   const bool resid = F != nullptr;
@@ -220,11 +222,11 @@ hipError_t stencil_launch(h6_plan P, const Tin* x, Tout* y, const double2* F, do
   hipEvent_t ev;
   timing_begin(P, resid ? KC_STENCIL_RESID : KC_STENCIL, s, &ev);
   if (resid)
-    hipLaunchKernelGGL((stencil_kernel<true, Tin, Tout, kTZ>), dim3(nwg), dim3(kThreads), 0, s, x, y, F,
+    hipLaunchKernelGGL((stencil_kernel<true, Tin, Tout, kTX, kTZ>), dim3(nwg), dim3(kThreads), 0, s, x, y, F,
                        partials, fpartials, P->d_stencil, nx, ny, nz, P->xmirror, P->ymirror, P->zlo_closure,
                        P->zhi_closure, ntx, nty, nwg, P->skip);
   else
-    hipLaunchKernelGGL((stencil_kernel<false, Tin, Tout, kTZ>), dim3(nwg), dim3(kThreads), 0, s, x, y,
+    hipLaunchKernelGGL((stencil_kernel<false, Tin, Tout, kTX, kTZ>), dim3(nwg), dim3(kThreads), 0, s, x, y,
                        nullptr, nullptr, nullptr, P->d_stencil, nx, ny, nz, P->xmirror, P->ymirror,
                        P->zlo_closure, P->zhi_closure, ntx, nty, nwg, P->skip);
   timing_end(P, resid ? KC_STENCIL_RESID : KC_STENCIL, s, ev,
@@ -233,13 +235,20 @@ hipError_t stencil_launch(h6_plan P, const Tin* x, Tout* y, const double2* F, do
   return hipGetLastError();
 }
 
-// the plan's z-chunk depth (set by the autotuner; 16 by default)
+// the plan's tile width and z-chunk depth (stencil_defaults; the depth may be autotuned)
 template <typename Tin, typename Tout>
 hipError_t stencil_impl(h6_plan P, const Tin* x, Tout* y, const double2* F, double* partials,
                         int* nparts, hipStream_t s, double* fpartials = nullptr) {
-  if (P->stencil_tz == 8) return stencil_launch<Tin, Tout, 8>(P, x, y, F, partials, nparts, s, fpartials);
-  if (P->stencil_tz == 32) return stencil_launch<Tin, Tout, 32>(P, x, y, F, partials, nparts, s, fpartials);
-  return stencil_launch<Tin, Tout, 16>(P, x, y, F, partials, nparts, s, fpartials);
+  auto go = [&](auto tx) {
+    switch (P->stencil_tz) {
+      case 2: return stencil_launch<Tin, Tout, tx(), 2>(P, x, y, F, partials, nparts, s, fpartials);
+      case 4: return stencil_launch<Tin, Tout, tx(), 4>(P, x, y, F, partials, nparts, s, fpartials);
+      case 8: return stencil_launch<Tin, Tout, tx(), 8>(P, x, y, F, partials, nparts, s, fpartials);
+      case 32: return stencil_launch<Tin, Tout, tx(), 32>(P, x, y, F, partials, nparts, s, fpartials);
+      default: return stencil_launch<Tin, Tout, tx(), 16>(P, x, y, F, partials, nparts, s, fpartials);
+    }
+  };
+  return P->stencil_tx == 32 ? go(std::integral_constant<int, 32>{}) : go(std::integral_constant<int, 64>{});
 }
 
 hipError_t launch_stencil(h6_plan P, const double2* x, double2* y, const double2* F,
@@ -251,9 +260,26 @@ hipError_t launch_stencil_f32in(h6_plan P, const float2* x, double2* y, hipStrea
   return stencil_impl(P, x, y, static_cast<const double2*>(nullptr), nullptr, nullptr, s);
 }
 
+bool stencil_tz_ok(int tz) { return tz == 2 || tz == 4 || tz == 8 || tz == 16 || tz == 32; }
+
 int stencil_workgroups(h6_plan P) {
-  const int tz = P->stencil_tz == 8 || P->stencil_tz == 32 ? P->stencil_tz : 16;
-  return ((P->dims[0] + kTX - 1) / kTX) * ((P->dims[1] + kTY - 1) / kTY) * ((P->dims[2] + tz - 1) / tz);
+  const int tx = P->stencil_tx, ty = 512 / tx, tz = P->stencil_tz;
+  return ((P->dims[0] + tx - 1) / tx) * ((P->dims[1] + ty - 1) / ty) * ((P->dims[2] + tz - 1) / tz);
+}
+
+// The tile is 32 wide where that wastes fewer lanes (n'x = 160: 26.5 against
+// 29.3 us, 200 x 163 x 99: 22.1 against 24.4), else 64.  A workgroup walks its
+// chunk plane by plane, one load latency each, so a small grid needs shallow
+// chunks to have enough of them in flight, a large one deep chunks to read its
+// halo planes less often: the deepest chunk that leaves about four workgroups
+// per CU.  Chunks of 2 / 4 / 8 / 16 planes, apply_A: 32^3 8.1 / 8.3 / 9.7 / 15.2 us,
+// 128^3 20.5 / 17.3 / 18.3 / 22.5, 160^3 36.0 / 27.8 / 26.5 / 29.6, 256^3 169 / 134 /
+// 121 / 121.
+void stencil_defaults(h6_plan P) {
+  const int nx = P->dims[0];
+  P->stencil_tx = (nx + 31) / 32 * 32 < (nx + 63) / 64 * 64 ? 32 : 64;
+  for (P->stencil_tz = 16; P->stencil_tz > 2; P->stencil_tz /= 2)
+    if (stencil_workgroups(P) >= 1000) break;
 }
 
 hipError_t launch_resid_f32out(h6_plan P, const double2* U, float2* r, const double2* F,
