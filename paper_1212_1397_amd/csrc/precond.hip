@@ -122,7 +122,7 @@ template <typename R, int kLanes, int kSegs, int kSmax>
 __global__ __launch_bounds__(kLanes * kSegs) void tridiag_z_kernel(
     const typename C2<R>::T* __restrict__ in, typename C2<R>::T* __restrict__ out,
     const typename C2<R>::T* __restrict__ cstart, const double* __restrict__ lx,
-    const double* __restrict__ ly, const double* __restrict__ zp, int nx, int ny, int nz,
+    const double* __restrict__ ly, const double* __restrict__ zp, int nx, int ny, int nz, int remap,
     const int* __restrict__ skip) {
   if (skip && *skip) return;
   // kappa and the scaled end rows (ZEnds), from device memory (kZParams doubles)
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kLanes * kSegs) void tridiag_z_kernel(
   const int lane = tid % kLanes;
   const int seg = tid / kLanes;
   const int nmodes = nx * ny;
-  const int mode = blockIdx.x * kLanes + lane;
+  const int mode = (remap ? xcd_remap(blockIdx.x, gridDim.x) : int(blockIdx.x)) * kLanes + lane;
   const bool active = mode < nmodes;
   const int mc = active ? mode : nmodes - 1;
   const int i = mc % nx, j = mc / nx;
@@ -263,9 +263,15 @@ hipError_t pinv_impl(h6_plan P, const Tin* r, Tout* z, hipStream_t s, int part, 
   timing_begin(P, KC_TRIDIAG, s, &ev);
   {
     const T2* cst = static_cast<const T2*>(P->d_cstart);
+    // neighbouring mode groups share 128-byte lines where a plane is not a
+    // multiple of the group, and DRAM pages anyway: vectors beyond the caches
+    // keep them under one L2 (255 x 255 x 256: 189 -> 148 us in complex128, 86 ->
+    // 70 in complex64; 511 x 511 x 512 1420 -> 1042; 256 x 258 x 258 complex64 68 ->
+    // 65).  Cache-resident ones do not (127 x 127 x 128 complex64 14 -> 16 us).
+    const int remap = P->N * sizeof(T2) > (size_t(48) << 20);
     auto go = [&](auto kern, int lanes) {
       hipLaunchKernelGGL(kern, dim3((nx * ny + lanes - 1) / lanes), dim3(512), 0, s, w1, w0, cst,
-                         P->d_lambda_x, P->d_lambda_y, P->d_zparams, nx, ny, nz, P->skip);
+                         P->d_lambda_x, P->d_lambda_y, P->d_zparams, nx, ny, nz, remap, P->skip);
     };
     if (z_segments(nz, sizeof(R) == 4) == 16) {
       if (nz <= 16 * 5) go(tridiag_z_kernel<R, 32, 16, 5>, 32);
