@@ -7,8 +7,8 @@
 //     channels, k = two taps x 16 channels of one input chunk, the input
 //     block and a tap pair's weights staged in LDS;
 //   weight gradient (v_mfma_f32_16x16x16bf16_1k): rows = output channels,
-//     columns = input channels, k = voxels, one tap per workgroup,
-//     deterministic two-stage reduction.
+//     columns = input channels, k = voxels, all taps of a voxel block in one
+//     workgroup, deterministic two-stage reduction.
 // Operand lane layouts (lane l; K = 16: e = 0..3, K = 32: e = 0..7):
 //   K = 16: A[l % 16][4 (l / 16) + e], B[4 (l / 16) + e][l % 16];
 //   K = 32: A[l % 16][8 (l / 16) + e], B[8 (l / 16) + e][l % 16];
@@ -338,198 +338,124 @@ __global__ __launch_bounds__(256) void conv_tile_x32_kernel(View in, const bf16*
   }
 }
 
-constexpr int kWgTile = 64;      // voxels per weight-gradient tile
-constexpr int kWgStride = 68;    // LDS row stride (bf16) of the transposed tiles
+// Weight gradient: a workgroup walks 16 x 4 x 4 voxel blocks (grid-stride) for 16
+// input and 16 NA output channels (blockIdx.y: which), stages the block's output
+// gradient (dzs[v][co]) and its input with the one-voxel halo (xh[hv][ci]) in
+// LDS and forms dW[tap][co][ci] += sum_v dz[v][co] x[v + tap][ci] for all 27 taps
+// by v_mfma_f32_16x16x16_bf16 (rows co, columns ci, k = voxels).  Both operands
+// need four voxels of one channel per lane, which gfx950's transposing LDS read
+// (ds_read_b64_tr_b16) gives straight from the voxel-major tiles.  Wave w takes
+// the nine taps of one x offset: it holds the block's 16 rows of dz in registers
+// and reads each of the 36 halo rows of x once for up to nine products (one LDS
+// read per 4 NA products; five reads per product, with two-byte reads and taps
+// shared out over the waves, took 41 us per 16 -> 16 layer at 64 x 66 x 66).
+// Partials per workgroup, summed in order by wgrad_reduce_kernel; bias partials
+// sum dz over the same voxels.
+constexpr int kWgThreads = 192;
+constexpr int kWgRows = 768;      // workgroups aimed at: three per CU
 
-// Partial weight gradients of one tap over a strided set of voxel tiles:
-//   part[g][tap][co][ci] = sum_v dz[v][co] x[v + tap][ci]
-// and (centre tap) the bias partials bpart[g][co] = sum_v dz[v][co].
-template <int CINP, int COUTP>
-__global__ __launch_bounds__(256) void wgrad_kernel(View dz, View xin, float* __restrict__ part,
-                                                    float* __restrict__ bpart, Grid3 g) {
-  __shared__ __attribute__((aligned(16))) bf16 dzT[COUTP * kWgStride];
-  __shared__ __attribute__((aligned(16))) bf16 xT[CINP * kWgStride];
-  constexpr int NA = COUTP / 16, NB = CINP / 16, NPAIR = NA * NB;
-  constexpr int PW = (NPAIR + 3) / 4;        // pairs per wave
-  const int tap = blockIdx.x, gi = blockIdx.y, G = gridDim.y;
-  const int dzt = tap / 9 - 1, dyt = (tap / 3) % 3 - 1, dxt = tap % 3 - 1;
-  const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, i = l & 15, kq = l >> 4;
-  const long long P = g.P();
-  const long long ntiles = (P + kWgTile - 1) / kWgTile;
-  f4 acc[PW];
-#pragma unroll
-  for (int q = 0; q < PW; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
-  float bsum = 0.f;
-  for (long long tl = gi; tl < ntiles; tl += G) {
-    const long long v0 = tl * kWgTile;
-    // stage dz (transposed) and the tap-shifted input (transposed, zero outside)
-    for (int idx = tid; idx < kWgTile * (COUTP / 4); idx += 256) {
-      const int vv = idx / (COUTP / 4), cq = idx % (COUTP / 4);
-      const long long v = v0 + vv;
-      s4 a = s4{0, 0, 0, 0};
-      if (v < P) a = *reinterpret_cast<const s4*>(dz.p + v * dz.cs + dz.coff + 4 * cq);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) dzT[(4 * cq + e) * kWgStride + vv] = bf16(a[e]);
-    }
-    for (int idx = tid; idx < kWgTile * (CINP / 4); idx += 256) {
-      const int vv = idx / (CINP / 4), cq = idx % (CINP / 4);
-      const long long v = v0 + vv;
-      s4 a = s4{0, 0, 0, 0};
-      if (v < P) {
-        const int x = int(v % g.X), y = int((v / g.X) % g.Y), z = int(v / ((long long)g.X * g.Y));
-        if (x + dxt >= 0 && x + dxt < g.X && y + dyt >= 0 && y + dyt < g.Y && z + dzt >= 0 && z + dzt < g.Z) {
-          const long long nv = v + dxt + (long long)g.X * (dyt + (long long)g.Y * dzt);
-          a = *reinterpret_cast<const s4*>(xin.p + nv * xin.cs + xin.coff + 4 * cq);
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) xT[(4 * cq + e) * kWgStride + vv] = bf16(a[e]);
-    }
-    __syncthreads();
-    if (tap == 13 && tid < COUTP)
-      for (int vv = 0; vv < kWgTile; ++vv) bsum += bf2f(dzT[tid * kWgStride + vv]);
-#pragma unroll
-    for (int q = 0; q < PW; ++q) {
-      const int pr = wave + 4 * q;
-      if (pr < NPAIR) {
-        const int ta = pr / NB, tb = pr % NB;
-#pragma unroll
-        for (int kc = 0; kc < kWgTile / 16; ++kc) {
-          const s4 a = *reinterpret_cast<const s4*>(&dzT[(ta * 16 + i) * kWgStride + kc * 16 + 4 * kq]);
-          const s4 b = *reinterpret_cast<const s4*>(&xT[(tb * 16 + i) * kWgStride + kc * 16 + 4 * kq]);
-          acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[q], 0, 0, 0);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  float* dst = part + ((size_t)gi * 27 + tap) * COUTP * CINP;
-#pragma unroll
-  for (int q = 0; q < PW; ++q) {
-    const int pr = wave + 4 * q;
-    if (pr < NPAIR) {
-      const int ta = pr / NB, tb = pr % NB;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) dst[(ta * 16 + 4 * kq + e) * CINP + tb * 16 + i] = acc[q][e];
-    }
-  }
-  if (tap == 13 && tid < COUTP) bpart[(size_t)gi * COUTP + tid] = bsum;
+typedef __attribute__((address_space(3))) s4 lds_s4;
+__device__ __forceinline__ s4 lds_tr(const bf16* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p));
 }
 
-// Weight gradient with all 27 taps in one workgroup (layers with at most
-// three 16 x 16 channel tiles): a workgroup walks 16 x 4 x 4 voxel blocks
-// (grid-stride), stages the block's output gradient transposed (dzT[co][v])
-// and its input with the one-voxel halo (xh[hv][ci]) in LDS once, and every
-// wave accumulates the products of its taps (w, w + 4, ...) over the block's
-// 256 voxels: dW[tap][co][ci] += sum_v dz[v][co] x[v + tap][ci] (rows co,
-// columns ci, k = voxels).  Partials per workgroup, summed in order by
-// wgrad_reduce_kernel; bias partials sum dz over the same voxels.
-constexpr int kWgTileGroups = 512;
-
-template <int CINP, int COUTP>
-__global__ __launch_bounds__(256) void wgrad_tile_kernel(View dz, View xin, float* __restrict__ part,
-                                                         float* __restrict__ bpart, Grid3 g, int ntx,
-                                                         int nty, int nblocks) {
-  constexpr int NA = COUTP / 16, NB = CINP / 16, NPAIR = NA * NB;
-  constexpr int HV = kHX * kHY * kHZ, NV = kTX * kTY * kTZ;
-  constexpr int DS = NV + 4;                          // dzT row stride (bf16)
-  constexpr int NTT = 7;                              // taps per wave (27 = 4 x 7 - 1)
-  static_assert(256 % COUTP == 0, "bias partials: whole channel groups per workgroup");
-  __shared__ __attribute__((aligned(16))) bf16 dzT[COUTP * DS];
-  __shared__ __attribute__((aligned(16))) bf16 xh[HV * CINP];
+template <int NA>
+__global__ __launch_bounds__(kWgThreads) void wgrad_kernel(View dz, View xin, float* __restrict__ part,
+                                                           float* __restrict__ bpart, Grid3 g, int ntx, int nty,
+                                                           int nblocks, int cinp, int coutp) {
+  constexpr int HV = kHX * kHY * kHZ, NV = kTX * kTY * kTZ, CO = 16 * NA;
+  __shared__ __attribute__((aligned(16))) bf16 dzs[NV * CO];
+  __shared__ __attribute__((aligned(16))) bf16 xh[HV * 16];
+  __shared__ float bred[kWgThreads];
   const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, i = l & 15, kq = l >> 4;
-  f4 acc[NTT][NPAIR];
+  const int nci = cinp / 16, ci0 = 16 * (blockIdx.y % nci), co0 = CO * (blockIdx.y / nci);
+  const bool bias = ci0 == 0;
+  // transposing read: lane l of a 16-lane group addresses voxel (l & 15) / 4 of the
+  // group's four, channels 4 (l & 3) ..; it receives channel l & 15 of the four
+  const int tv = 4 * kq + (i >> 2), tc = 4 * (i & 3);
+  f4 acc[9][NA];
 #pragma unroll
-  for (int tt = 0; tt < NTT; ++tt)
+  for (int t = 0; t < 9; ++t)
 #pragma unroll
-    for (int q = 0; q < NPAIR; ++q) acc[tt][q] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < NA; ++q) acc[t][q] = f4{0.f, 0.f, 0.f, 0.f};
   float bsum = 0.f;
   for (int blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
     const int bx = blk % ntx, by = (blk / ntx) % nty, bz = blk / (ntx * nty);
     const int x0 = bx * kTX, y0 = by * kTY, z0 = bz * kTZ;
     __syncthreads();                                  // the previous block's reads are done
-    for (int idx = tid; idx < NV * (COUTP / 4); idx += 256) {
-      const int v = idx / (COUTP / 4), cq = idx % (COUTP / 4);
+    for (int idx = tid; idx < NV * 2 * NA; idx += kWgThreads) {
+      const int v = idx / (2 * NA), c8 = 8 * (idx % (2 * NA));
       const int gx = x0 + (v & 15), gy = y0 + ((v >> 4) & 3), gz = z0 + (v >> 6);
-      s4 a = s4{0, 0, 0, 0};
-      if (gx < g.X && gy < g.Y && gz < g.Z) {
-        const long long gv = gx + (long long)g.X * (gy + (long long)g.Y * gz);
-        a = *reinterpret_cast<const s4*>(dz.p + gv * dz.cs + dz.coff + 4 * cq);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) dzT[(4 * cq + e) * DS + v] = bf16(a[e]);
+      u4w a = u4w{0u, 0u, 0u, 0u};
+      if (gx < g.X && gy < g.Y && gz < g.Z)
+        a = *reinterpret_cast<const u4w*>(dz.p + (gx + (long long)g.X * (gy + (long long)g.Y * gz)) * dz.cs + dz.coff +
+                                          co0 + c8);
+      *reinterpret_cast<u4w*>(&dzs[v * CO + c8]) = a;
     }
-    for (int idx = tid; idx < HV * (CINP / 4); idx += 256) {
-      const int hv = idx / (CINP / 4), cq = idx % (CINP / 4);
+    for (int idx = tid; idx < HV * 2; idx += kWgThreads) {
+      const int hv = idx >> 1, c8 = 8 * (idx & 1);
       const int hx = hv % kHX, hy = (hv / kHX) % kHY, hz = hv / (kHX * kHY);
       const int gx = x0 - 1 + hx, gy = y0 - 1 + hy, gz = z0 - 1 + hz;
-      s4 a = s4{0, 0, 0, 0};
-      if (gx >= 0 && gx < g.X && gy >= 0 && gy < g.Y && gz >= 0 && gz < g.Z) {
-        const long long gv = gx + (long long)g.X * (gy + (long long)g.Y * gz);
-        a = *reinterpret_cast<const s4*>(xin.p + gv * xin.cs + xin.coff + 4 * cq);
-      }
-      *reinterpret_cast<s4*>(&xh[hv * CINP + 4 * cq]) = a;
+      u4w a = u4w{0u, 0u, 0u, 0u};
+      if (unsigned(gx) < unsigned(g.X) && unsigned(gy) < unsigned(g.Y) && unsigned(gz) < unsigned(g.Z))
+        a = *reinterpret_cast<const u4w*>(xin.p + (gx + (long long)g.X * (gy + (long long)g.Y * gz)) * xin.cs +
+                                          xin.coff + ci0 + c8);
+      *reinterpret_cast<u4w*>(&xh[hv * 16 + c8]) = a;
     }
     __syncthreads();
-    // bias partials: thread tid sums channel tid % COUTP over voxels tid / COUTP + k 256 / COUTP
-    for (int v = tid / COUTP; v < NV; v += 256 / COUTP) bsum += bf2f(dzT[(tid % COUTP) * DS + v]);
+    // bias partials: thread tid sums channel tid % CO over voxels tid / CO + k kWgThreads / CO
+    if (bias)
+      for (int v = tid / CO; v < NV; v += kWgThreads / CO) bsum += bf2f(dzs[v * CO + tid % CO]);
+    s4 a[16][NA];                                     // x rows of dz: y = r & 3, z = r >> 2
 #pragma unroll
-    for (int tt = 0; tt < NTT; ++tt) {
-      const int t = wave + 4 * tt;
-      if (t < 27) {
-        const int dxt = t % 3 - 1, dyt = (t / 3) % 3 - 1, dzt = t / 9 - 1;
-#pragma unroll 2
-        for (int kc = 0; kc < NV / 16; ++kc) {       // one x row of the block: y = kc & 3, z = kc >> 2
-          const int hrow = kHX * (((kc & 3) + 1 + dyt) + kHY * ((kc >> 2) + 1 + dzt)) + 1 + dxt;
-          s4 a[NA], b[NB];
+    for (int r = 0; r < 16; ++r)
 #pragma unroll
-          for (int ta = 0; ta < NA; ++ta)
-            a[ta] = *reinterpret_cast<const s4*>(&dzT[(ta * 16 + i) * DS + kc * 16 + 4 * kq]);
+      for (int q = 0; q < NA; ++q) a[r][q] = lds_tr(&dzs[(16 * r + tv) * CO + 16 * q + tc]);
 #pragma unroll
-          for (int tb = 0; tb < NB; ++tb)
+    for (int hz = 0; hz < kHZ; ++hz)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) b[tb][e] = short(xh[(hrow + 4 * kq + e) * CINP + tb * 16 + i]);
+      for (int hy = 0; hy < kHY; ++hy) {
+        const s4 b = lds_tr(&xh[(kHX * (hy + kHY * hz) + wave + tv) * 16 + tc]);
 #pragma unroll
-          for (int ta = 0; ta < NA; ++ta)
+        for (int z = 0; z < kTZ; ++z)
 #pragma unroll
-            for (int tb = 0; tb < NB; ++tb)
-              acc[tt][ta * NB + tb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[ta], b[tb], acc[tt][ta * NB + tb], 0, 0, 0);
-        }
+          for (int y = 0; y < kTY; ++y) {
+            const int dy = hy - y, dz3 = hz - z;      // tap offsets + 1
+            if (dy < 0 || dy > 2 || dz3 < 0 || dz3 > 2) continue;
+#pragma unroll
+            for (int q = 0; q < NA; ++q)
+              acc[3 * dz3 + dy][q] =
+                  __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[y + 4 * z][q], b, acc[3 * dz3 + dy][q], 0, 0, 0);
+          }
       }
-    }
   }
   const int gi = blockIdx.x;
 #pragma unroll
-  for (int tt = 0; tt < NTT; ++tt) {
-    const int t = wave + 4 * tt;
-    if (t < 27) {
-      float* dst = part + ((size_t)gi * 27 + t) * COUTP * CINP;
+  for (int t = 0; t < 9; ++t) {
+    float* dst = part + (((size_t)gi * 27 + 3 * t + wave) * coutp + co0) * cinp + ci0;
 #pragma unroll
-      for (int ta = 0; ta < NA; ++ta)
+    for (int q = 0; q < NA; ++q)
 #pragma unroll
-        for (int tb = 0; tb < NB; ++tb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dst[(ta * 16 + 4 * kq + e) * CINP + tb * 16 + i] = acc[tt][ta * NB + tb][e];
-    }
+      for (int e = 0; e < 4; ++e) dst[(q * 16 + 4 * kq + e) * cinp + i] = acc[t][q][e];
   }
-  // the 256 / COUTP bias partials of each channel, added in thread order
-  __shared__ float bred[256];
-  bred[tid] = bsum;
-  __syncthreads();
-  if (tid < COUTP) {
-    float t = 0.f;
-    for (int k = tid; k < 256; k += COUTP) t += bred[k];
-    bpart[(size_t)gi * COUTP + tid] = t;
+  if (bias) {          // the kWgThreads / CO bias partials of each channel, added in thread order
+    bred[tid] = bsum;
+    __syncthreads();
+    if (tid < CO) {
+      float t = 0.f;
+      for (int k = tid; k < kWgThreads; k += CO) t += bred[k];
+      bpart[(size_t)gi * coutp + co0 + tid] = t;
+    }
   }
 }
 
 // Second stage of the weight gradients: gw = sum over the G partial rows, in
-// the parameter layout.  A workgroup takes 64 consecutive entries of the
-// partial layout [tap][co][ci] (coalesced reads) and splits the rows four
-// ways (row q to slice q mod 4, each slice summed in row order); the four
-// slice sums are added in slice order, so the result is deterministic.
-// Workgroups past the weights do the bias rows the same way.
-constexpr int kWrW = 64, kWrS = 4;
+// the parameter layout.  A workgroup takes 32 consecutive entries of the
+// partial layout [tap][co][ci] (128-byte reads) and splits the rows 16 ways
+// (row q to slice q mod 16, each slice summed in row order, eight rows' loads in
+// flight); the slice sums are added in slice order, so the result is
+// deterministic.  Workgroups past the weights do the bias rows the same way.
+constexpr int kWrW = 32, kWrS = 16;
 __global__ __launch_bounds__(kWrW * kWrS) void wgrad_reduce_kernel(const float* __restrict__ part,
                                                                    const float* __restrict__ bpart, int G, int cin,
                                                                    int cout, int cinp, int coutp,
@@ -543,8 +469,19 @@ __global__ __launch_bounds__(kWrW * kWrS) void wgrad_reduce_kernel(const float* 
   const size_t stride = bias ? size_t(coutp) : size_t(npad);
   const float* __restrict__ src = bias ? bpart : part;
   float a = 0.f;
-  if (e < n)
-    for (int q = slice; q < G; q += kWrS) a += src[size_t(q) * stride + e];
+  if (e < n) {
+    constexpr int U = 8;
+    for (int q0 = slice; q0 < G; q0 += U * kWrS) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int q = q0 + u * kWrS;
+        v[u] = src[size_t(q < G ? q : slice) * stride + e];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) a += q0 + u * kWrS < G ? v[u] : 0.f;
+    }
+  }
   __shared__ float red[kWrS][kWrW];
   red[slice][lane] = a;
   __syncthreads();
@@ -823,8 +760,6 @@ long long param_count() {
   return n;
 }
 
-constexpr int kWgGroups = 64;     // workgroup rows of the weight-gradient reduction
-
 }  // namespace
 }  // namespace h6
 
@@ -913,44 +848,33 @@ hipError_t conv(View in, int cinp, const bf16* W, int coutp, const float* bias, 
   return hipErrorInvalidValue;
 }
 
-#define H6_WGRAD_TILE_CASES(X) X(16, 16) X(16, 32) X(48, 16)
-#define H6_WGT_PAIRS(CI, CO) (CI) * (CO),
-constexpr int kWgTilePairs[] = {H6_WGRAD_TILE_CASES(H6_WGT_PAIRS)};
-#undef H6_WGT_PAIRS
-// Largest channel-pair count of the tiled cases: sizes their partial rows.
-constexpr size_t wgrad_tile_pairs_max() {
-  size_t m = 0;
-  for (int p : kWgTilePairs) m = size_t(p) > m ? size_t(p) : m;
-  return m;
+// Partial rows of a layer with coutp x cinp channels: about kWgRows workgroups,
+// blockIdx.y taking the 16-channel input chunks and the output channels by 16 or
+// 32, with whole rounds of blocks per workgroup.
+int wgrad_chunks(int cinp, int coutp) { return cinp / 16 * (coutp == 16 ? 1 : coutp / 32); }
+int wgrad_rows(int nblocks, int chunks) {
+  const int most = kWgRows / chunks, rounds = (nblocks + most - 1) / most;
+  return (nblocks + rounds - 1) / rounds;
 }
-#define H6_WGRAD_CASES(X) X(16, 16) X(16, 32) X(32, 32) X(32, 64) X(64, 64) X(96, 32) X(48, 16)
+// floats of the partial rows of any layer: kWgRows / chunks rows of 27 coutp cinp,
+// and coutp cinp <= 512 chunks
+constexpr size_t kWgPartFloats = size_t(kWgRows) * 27 * 512;
 
 // weight-gradient partials of one layer; *groups = the number of partial rows
 hipError_t wgrad(View dz, View xin, int cinp, int coutp, float* part, float* bpart, Grid3 g,
                  hipStream_t s, int* groups) {
-  {
-    const int ntx = (g.X + kTX - 1) / kTX, nty = (g.Y + kTY - 1) / kTY, ntz = (g.Z + kTZ - 1) / kTZ;
-    const int nblocks = ntx * nty * ntz;
-#define H6_WGT(CI, CO)                                                                               \
-  if (cinp == CI && coutp == CO) {                                                                   \
-    hipLaunchKernelGGL((wgrad_tile_kernel<CI, CO>), dim3(kWgTileGroups), dim3(256), 0, s, dz, xin,   \
-                       part, bpart, g, ntx, nty, nblocks);                                           \
-    *groups = kWgTileGroups;                                                                         \
-    return hipGetLastError();                                                                        \
-  }
-    H6_WGRAD_TILE_CASES(H6_WGT)
-#undef H6_WGT
-  }
-  *groups = kWgGroups;
-#define H6_WG(CI, CO)                                                                              \
-  if (cinp == CI && coutp == CO) {                                                                 \
-    hipLaunchKernelGGL((wgrad_kernel<CI, CO>), dim3(27, kWgGroups), dim3(256), 0, s, dz, xin, part, \
-                       bpart, g);                                                                  \
-    return hipGetLastError();                                                                      \
-  }
-  H6_WGRAD_CASES(H6_WG)
-#undef H6_WG
-  return hipErrorInvalidValue;
+  if (cinp % 16 || (coutp != 16 && coutp % 32)) return hipErrorInvalidValue;
+  const int ntx = (g.X + kTX - 1) / kTX, nty = (g.Y + kTY - 1) / kTY, ntz = (g.Z + kTZ - 1) / kTZ;
+  const int nblocks = ntx * nty * ntz, chunks = wgrad_chunks(cinp, coutp);
+  *groups = wgrad_rows(nblocks, chunks);
+  const dim3 grid(*groups, chunks);
+  if (coutp == 16)
+    hipLaunchKernelGGL(wgrad_kernel<1>, grid, dim3(kWgThreads), 0, s, dz, xin, part, bpart, g, ntx, nty, nblocks, cinp,
+                       coutp);
+  else
+    hipLaunchKernelGGL(wgrad_kernel<2>, grid, dim3(kWgThreads), 0, s, dz, xin, part, bpart, g, ntx, nty, nblocks, cinp,
+                       coutp);
+  return hipGetLastError();
 }
 
 View vw(bf16* p, int cs, int coff = 0) { return View{p, cs, coff}; }
@@ -1094,11 +1018,8 @@ hipError_t alloc_training(h6_net N) {
   A(&N->dY, p1 * 16); A(&N->dD1, p1 * 16); A(&N->dT1b, p1 * 16); A(&N->dC1, p1 * 48); A(&N->dT1, p1 * 16);
   A(&N->dD2, p2 * 32); A(&N->dT2b, p2 * 32); A(&N->dC2, p2 * 96); A(&N->dT2, p2 * 32); A(&N->dPl1, p2 * 16);
   A(&N->dB3, p3 * 64); A(&N->dT3, p3 * 64); A(&N->dPl2, p3 * 32);
-  // partial rows: kWgGroups of up to 96 x 64 channels, or kWgTileGroups of every tiled layer's pairs
-  static_assert(size_t(kWgTileGroups) * 27 * wgrad_tile_pairs_max() <= size_t(kWgGroups) * 27 * 96 * 64,
-                "wgrad partials");
-  if (e == hipSuccess) e = dalloc(N, &N->part, size_t(kWgGroups) * 27 * 96 * 64);
-  if (e == hipSuccess) e = dalloc(N, &N->bpart, size_t(kWgTileGroups) * 64);
+  if (e == hipSuccess) e = dalloc(N, &N->part, kWgPartFloats);
+  if (e == hipSuccess) e = dalloc(N, &N->bpart, size_t(kWgRows) * 64);
   if (e == hipSuccess) e = dalloc(N, &N->m, size_t(N->np));
   if (e == hipSuccess) e = dalloc(N, &N->v, size_t(N->np));
   return e;
