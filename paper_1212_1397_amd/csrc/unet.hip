@@ -2,10 +2,9 @@
 // BF16 activations and weights, FP32 accumulation on the matrix cores.
 //
 // Convolutions are implicit GEMMs on the matrix cores:
-//   forward / input gradient (v_mfma_f32_16x16x32_bf16): rows = voxels (a
-//     wave owns four 16-voxel rows of a 16 x 4 x 4 block), columns = output
-//     channels, k = two taps x 16 channels of one input chunk, the input
-//     block and a tap pair's weights staged in LDS;
+//   forward / input gradient (v_mfma_f32_16x16x32_bf16): rows = output
+//     channels, columns = voxels, k = two taps x 16 channels of one input
+//     chunk, the chunk's input block and weights staged in LDS;
 //   weight gradient (v_mfma_f32_16x16x16bf16_1k): rows = output channels,
 //     columns = input channels, k = voxels, all taps of a voxel block in one
 //     workgroup, deterministic two-stage reduction.
@@ -20,6 +19,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "h6_internal.h"
@@ -48,94 +48,93 @@ struct View {           // channels-last BF16 view
 };
 
 // Convolution out[v][co] = act(b[co] + sum_{tap, ci} W[tap][co][ci] in[v + tap][ci])
-// (zero outside the grid), CIN and COUTP multiples of 16; writes co < cout (BF16
-// view, or FP32 [v][2] when out32).  A workgroup owns a 16 x 4 x 4 block of
-// output voxels (wave w: z offset w, row tile m: y offset m, 16 voxels along x)
-// and stages the block's input with its one-voxel halo, 18 x 6 x 6 voxels of
-// one 16-channel chunk, in LDS (each input voxel is read from L2 about 2.5
-// times instead of once per tap).
+// (zero outside the grid) as an implicit GEMM on v_mfma_f32_16x16x32_bf16: rows =
+// output channels, columns = 16 voxels along x, k = two taps x 16 channels of one
+// input chunk (lanes 0-31 the first tap, 32-63 the second; tap 27 is zero weights).
+// A workgroup owns 16 x MT x 4 output voxels (wave w: z offset w, accumulator m: y
+// offset m) and 16 output channels; the input block with its one-voxel halo, one
+// 16-channel chunk at a time, and the chunk's weights sit in LDS.
+//
+// Three things were in the way, by counters: the vector memory path of the CU (76 %
+// busy with the weights that every wave loaded for itself), LDS reads waited for one
+// by one, and VALU work (900 instructions per wave).  So the input and the weights
+// go straight to LDS, 1 KB per instruction, the weights once per workgroup in
+// fragment order (pack_kernel); sched_products has the LDS reads ahead of their
+// products; with channels as rows a lane ends up with four channels of one voxel,
+// which it stores itself, no exchange through LDS.  128 x 130 x 130, us before and
+// after: 16 -> 16 54 -> 49, 48 -> 16 135 -> 98, 96 -> 32 on the half grid 73 -> 54, 32 -> 32
+// 43 -> 25, 64 -> 64 on the quarter grid 37 -> 19; the whole forward pass 563 -> 393
+// (650 TFLOP/s).  What is left is the overlap of loads and products (42 of the 98 us
+// are matrix-core time).  Slower were two input buffers at two workgroups per CU
+// (through registers 135, straight to LDS 166 us for 48 -> 16) and workgroups that
+// walk blocks with the weights in registers (129).  Taking a halo row for its three
+// dy taps at once (half the LDS reads) gave no more and changes the order of the
+// sums, so the rounding of stored values.
+//
+// MODE 1: the first cu chunks of the input are the nearest-neighbour upsampling
+// of `up` (a grid of half the size, gu): voxel v reads up[v / 2], so the
+// decoder's concatenated input is never materialised; the other chunks come from
+// `in`.  MODE 2 (first layer, inference): the input is formed from the residual
+// fr: channels r re / rms, r im / rms, kh (zero for r = 0) and zeros, with
+// rms^2 = *fnrm / voxels (the features of h6net.h).
 constexpr int kTX = 16, kTY = 4, kTZ = 4;
 constexpr int kHX = kTX + 2, kHY = kTY + 2, kHZ = kTZ + 2;
+constexpr int kPairs = 14;       // the 27 taps (dx + 3 dy + 9 dz) two at a time
 
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef unsigned int u4w __attribute__((ext_vector_type(4)));
+typedef unsigned int u2w __attribute__((ext_vector_type(2)));
 
-// The tiled convolution on the K = 32 instruction: two taps per instruction
-// (lanes 0-31 the first tap's channels of a 16-channel chunk, 32-63 the
-// second's), the input block of one chunk in LDS and the weight fragments
-// read by each lane straight from the (L2-resident) packed weights into
-// registers a few steps ahead, so the steps s = (chunk, tap pair) run without
-// workgroup barriers; the next chunk's input block is loaded into registers
-// halfway through a chunk and stored to LDS between chunks.
-// Rows (y extent of the block, 16-voxel MFMA rows per wave) of the forward
-// convolution's output block for COUTP output channels: 8 up to 32 channels,
-// 4 above (accumulator registers).
-__host__ __device__ constexpr int conv_rows(int coutp) { return coutp <= 32 ? 8 : 4; }
-
-// voxel offset of tap t (t = dx + 3 dy + 9 dz over -1..1 each, + 13) inside an
-// LDS input block of row length kHX and HY rows per plane
+// voxel offset of tap t from tap 0 inside an LDS input block of HY rows per plane
 template <int HY>
 __host__ __device__ constexpr int tap_off(int t) {
-  return (t % 3 - 1) + kHX * ((t / 3) % 3 - 1) + kHX * HY * (t / 9 - 1);
+  return t % 3 + kHX * (t / 3 % 3) + kHX * HY * (t / 9);
 }
 
-// The tiled convolution on the K = 32 instruction: a workgroup owns a block
-// of 16 x MT x 4 output voxels (wave w: z offset w, MFMA row m: y offset m,
-// 16 voxels along x), two taps per instruction (lanes 0-31 the first tap's
-// channels of a 16-channel chunk, 32-63 the second's).  The input block of
-// one chunk with its one-voxel halo sits in LDS; the weight fragments are
-// read by each lane straight from the (L2-resident) packed weights into
-// registers a few steps ahead, so the steps (chunk, tap pair) run without
-// workgroup barriers; the next chunk's input block is loaded into registers
-// halfway through a chunk and stored to LDS between chunks.  BF16 results go
-// through LDS so that every lane stores 16-byte pieces (8 channels of one
-// voxel).  With CU > 0 the first CU chunks of the input are the nearest-
-// neighbour upsampling of `up` (a grid of half the size, gu): voxel v reads
-// up[v / 2], so the decoder's concatenated input is never materialised; the
-// remaining chunks come from `in`.  With CU < 0 (first layer, inference) the
-// input is formed on the fly from the residual fr: channels r re / rms,
-// r im / rms, kh (zero for r = 0) and zeros, with rms^2 = *fnrm / voxels
-// (the features of h6net.h), so that array is never materialised.
-// (Workgroups that march over several z blocks, reusing the x-y
-// part of the gather offsets, measured slower: the compiler keeps more
-// registers live across the march.)
-template <int CIN, int COUTP, int CU>
-__global__ __launch_bounds__(256) void conv_tile_x32_kernel(View in, const bf16* __restrict__ W,
-                                                            const float* __restrict__ bias, View out,
-                                                            float* __restrict__ out32, int cout, int relu,
-                                                            Grid3 g, int ntx, int nty, View up, Grid3 gu,
-                                                            const double2* __restrict__ fr,
-                                                            const double* __restrict__ fnrm, float fkh,
-                                                            View pout, Grid3 gp) {
-  constexpr int NT = COUTP / 16, KC = CIN / 16, MT = conv_rows(COUTP), HY = MT + 2;
-  constexpr int NP = 14;                              // tap pairs per chunk (the last one: tap 26 + zeros)
-  constexpr int HV = kHX * HY * kHZ;
+// Instruction order of a chunk's products: every LDS row is read kAhead products
+// ahead, a step's weights during the step before (left alone, the compiler waits
+// for each read in turn).
+constexpr int kAhead = 4;
+template <int MT, int N>
+__device__ __forceinline__ void sched_products() {
+  constexpr int total = kPairs * MT;
+  constexpr int reads = (N + kAhead < total ? 1 : 0) + (N % MT == 0 && N / MT + 1 < kPairs ? 1 : 0);
+  if constexpr (N == 0) __builtin_amdgcn_sched_group_barrier(0x100, 1 + kAhead, 0);  // 0x100: LDS reads
+  __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);                                   // 0x8: matrix products
+  if constexpr (reads > 0) __builtin_amdgcn_sched_group_barrier(0x100, reads, 0);
+  if constexpr (N + 1 < total) sched_products<MT, N + 1>();
+}
+
+typedef __attribute__((address_space(1))) const void gvoid;
+typedef __attribute__((address_space(3))) void lvoid;
+
+template <int MT, int MODE, bool MULTI>
+__global__ __launch_bounds__(256, 3) void conv_kernel(View in, const bf16* __restrict__ W, const float* __restrict__ bias,
+                                                      View out, float* __restrict__ out32, int nchunks, int ntall,
+                                                      int relu, Grid3 g, int ntx, int nty, View up, Grid3 gu,
+                                                      int cu, const double2* __restrict__ fr,
+                                                      const double* __restrict__ fnrm, float fkh, View pout, Grid3 gp) {
+  constexpr int HY = MT + 2, HV = kHX * HY * kHZ;
   constexpr int NPIECE = HV * 2, NPER = (NPIECE + 255) / 256;   // 16-byte pieces of an input block
-  constexpr size_t TAPW = size_t(COUTP) * CIN;        // weights per tap
-  constexpr int OV = 16 * MT;                         // output voxels per wave
-  constexpr int LDS_IN = HV * 32, LDS_OUT = 4 * OV * COUTP * 2;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_IN > LDS_OUT ? LDS_IN : LDS_OUT];
-  bf16 (*xs)[16] = reinterpret_cast<bf16 (*)[16]>(lds);
-  const int tid = threadIdx.x, l = tid & 63, wave = tid >> 6;
+  static_assert(4 * 16 * MT <= HV, "results to be pooled fit the input buffer");
+  __shared__ __attribute__((aligned(16))) bf16 xs[HV][16];
+  __shared__ u4w ws[kPairs][64];
+  const int tid = threadIdx.x, l = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = l & 15, half = (l >> 4) & 1, second = l >> 5;
-  const int bx = blockIdx.x % ntx, by = (blockIdx.x / ntx) % nty, bz = blockIdx.x / (ntx * nty);
-  const int x0 = bx * kTX, y0 = by * MT, z0 = bz * kTZ;
-  // gather offsets of this thread's pieces of the input block (element offsets
-  // of channel 4 q of the source's first chunk; -1 outside the grid), the
-  // same for every chunk of one source; sh = 1: voxel v of the grid reads
-  // voxel v / 2 of the source
-  int goff[NPER];
-  // fn(k, gx, gy, gz, inside) for this thread's pieces k: piece k is channel
-  // octet q = tid & 1 of block voxel hv = tid / 2 + 128 k, walked
-  // incrementally (128 voxels = 128 / kHX rows + 128 % kHX) instead of
-  // dividing per piece
+  // a block's channel groups and neighbouring blocks (shared halos) run under one L2
+  const int lid = xcd_remap(blockIdx.x, gridDim.x), t0 = lid % ntall, blk = lid / ntall;
+  struct Org { int x, y, z; };
+  const Org o{blk % ntx * kTX, blk / ntx % nty * MT, blk / (ntx * nty) * kTZ};
+  // staging: piece tid + 256 k (k < NPER) is channel octet tid & 1 of block voxel
+  // tid / 2 + 128 k, walked instead of divided.  fn(k, gx, gy, gz, inside)
+  const int q8 = 8 * (tid & 1);
   auto for_pieces = [&](auto&& fn) {
     const int hv0 = tid >> 1;
     int hx = hv0 % kHX, hy = (hv0 / kHX) % HY, hz = hv0 / (kHX * HY);
     static_assert(128 / kHX + 1 < 2 * HY, "at most two plane wraps per step");
 #pragma unroll
     for (int k = 0; k < NPER; ++k) {
-      const int gx = x0 - 1 + hx, gy = y0 - 1 + hy, gz = z0 - 1 + hz;
+      const int gx = o.x - 1 + hx, gy = o.y - 1 + hy, gz = o.z - 1 + hz;
       const bool inside = hz < kHZ && unsigned(gx) < unsigned(g.X) && unsigned(gy) < unsigned(g.Y) &&
                           unsigned(gz) < unsigned(g.Z);
       fn(k, gx, gy, gz, inside);
@@ -151,189 +150,155 @@ __global__ __launch_bounds__(256) void conv_tile_x32_kernel(View in, const bf16*
       }
     }
   };
-  const int q8 = 8 * (tid & 1);
-  // gather offsets (element offsets of channel 4 q of the source's first
-  // chunk; -1 outside the grid), the same for every chunk of one source;
-  // sh = 1: voxel v of the grid reads voxel v / 2 of the source
+  // byte offsets of this thread's pieces in the source's first chunk (they fit 32
+  // bits, see h6net_create), the same for every chunk of one source; a bit of
+  // `outside` per piece out of the grid.  sh = 1: voxel v reads voxel v / 2
+  unsigned goff[NPER], outside = 0;
   auto set_offsets = [&](const View& v, Grid3 gs, int sh) {
     for_pieces([&](int k, int gx, int gy, int gz, bool inside) {
-      goff[k] = inside ? ((gx >> sh) + gs.X * ((gy >> sh) + gs.Y * (gz >> sh))) * v.cs + v.coff + q8 : -1;
+      goff[k] = 2u * unsigned(((gx >> sh) + gs.X * ((gy >> sh) + gs.Y * (gz >> sh))) * v.cs + v.coff + q8);
+      if (!inside) outside |= 1u << k;
     });
   };
-  u4w xv[NPER];
-  if (CU < 0) {      // features from the residual (channels 0..2 of octet 0, zeros elsewhere)
+  // chunk kc of the input (channels 16 kc .. 16 kc + 15) and its weights, straight to LDS
+  const int nc = MULTI ? nchunks : 1;
+  auto load = [&](int kc) {
+    for (int n = wave; n < kPairs; n += 4)
+      __builtin_amdgcn_global_load_lds((gvoid*)(reinterpret_cast<const u4w*>(W) + ((kc * kPairs + n) * ntall + t0) * 64 + l),
+                                       (lvoid*)ws[n], 16, 0, 0);
+    if (MODE == 2) return;
+    const bool hi = MODE == 1 && kc < cu;
+    const char* src = reinterpret_cast<const char*>((hi ? up.p : in.p) + 16 * (MODE == 1 && !hi ? kc - cu : kc));
+#pragma unroll
+    for (int k = 0; k < NPER; ++k)
+      if (!(outside >> k & 1))
+        __builtin_amdgcn_global_load_lds((gvoid*)(src + goff[k]), (lvoid*)(&xs[0][0] + (256 * k + 64 * wave) * 8), 16, 0,
+                                         0);
+  };
+  if (MODE == 2) {      // features from the residual (channels 0..2 of octet 0, zeros elsewhere)
+    load(0);
     const double ms = *fnrm / double(g.P());
     const double inv = ms > 0.0 ? 1.0 / sqrt(ms) : 0.0;
     const unsigned kb = f2bf(ms > 0.0 ? fkh : 0.f);
+    double2 a[NPER];
+    bool in_grid[NPER];
     for_pieces([&](int k, int gx, int gy, int gz, bool inside) {
-      xv[k] = u4w{0u, 0u, 0u, 0u};
-      if (inside && q8 == 0) {
-        const double2 a = fr[gx + g.X * (gy + g.Y * gz)];
-        xv[k] = u4w{unsigned(f2bf(float(a.x * inv))) | (unsigned(f2bf(float(a.y * inv))) << 16), kb, 0u, 0u};
-      }
+      in_grid[k] = inside && q8 == 0;
+      a[k] = fr[in_grid[k] ? gx + g.X * (gy + g.Y * gz) : 0];
     });
+#pragma unroll
+    for (int k = 0; k < NPER; ++k) {
+      u4w v = {unsigned(f2bf(float(a[k].x * inv))) | (unsigned(f2bf(float(a[k].y * inv))) << 16), kb, 0u, 0u};
+      if (!in_grid[k]) v = u4w{0u, 0u, 0u, 0u};
+      if (tid + 256 * k < NPIECE) *reinterpret_cast<u4w*>(&xs[0][0] + (tid + 256 * k) * 8) = v;
+    }
+  } else {
+    if (MODE == 1) set_offsets(up, gu, 1);
+    else set_offsets(in, g, 0);
+    load(0);
+    // zeros outside the grid: no load writes there
+    if (outside)
+#pragma unroll
+      for (int k = 0; k < NPER; ++k)
+        if ((outside >> k & 1) && tid + 256 * k < NPIECE)
+          *reinterpret_cast<u4w*>(&xs[0][0] + (tid + 256 * k) * 8) = u4w{0u, 0u, 0u, 0u};
   }
-  auto load_x = [&](int kc) {      // chunk kc of the input (channels 16 kc .. 16 kc + 15)
-    const bf16* src = (CU > 0 && kc < CU) ? up.p : in.p;
-    const int c0 = 16 * ((CU > 0 && kc >= CU) ? kc - CU : kc);
-#pragma unroll
-    for (int k = 0; k < NPER; ++k) {
-      xv[k] = *reinterpret_cast<const u4w*>(src + (goff[k] >= 0 ? goff[k] + c0 : 0));
-      if (goff[k] < 0) xv[k] = u4w{0u, 0u, 0u, 0u};
-    }
-  };
-  if (CU > 0)
-    set_offsets(up, gu, 1);
-  else if (CU == 0)
-    set_offsets(in, g, 0);
-  auto store_x = [&]() {
-#pragma unroll
-    for (int k = 0; k < NPER; ++k) {
-      const int idx = tid + 256 * k;
-      if (idx < NPIECE) *reinterpret_cast<u4w*>(&xs[idx >> 1][8 * (idx & 1)]) = xv[k];
-    }
-  };
-  // B fragments: lane (i, half, second) holds channels 16 kc + 8 half .. + 7 of
-  // output channel 16 t + i for tap 2 pp + second; tap 27 (pp = 13, second
-  // lanes) reads tap 26 and is zeroed
-  const int wlo = (second * COUTP + i) * CIN + 8 * half;
-  auto load_b = [&](int kc, int pp, u4w (&bf)[NT]) {
-    const bf16* wk = W + 2 * pp * TAPW + 16 * kc;
-    const int lo = wlo - ((pp == NP - 1 && second) ? int(TAPW) : 0);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      bf[t] = *reinterpret_cast<const u4w*>(wk + lo + 16 * t * CIN);
-      if (pp == NP - 1 && second) bf[t] = u4w{0u, 0u, 0u, 0u};
-    }
-  };
-  // LDS row of the lane's A fragment at tap offset 0: voxel (i + 1, m + 1, wave + 1)
-  const int abase = (i + 1) + kHX * (1 + HY * (wave + 1));
-  constexpr int D = NT == 1 ? 6 : (NT == 2 ? 4 : 2);    // weight fragments are loaded D steps ahead
   {
-    if (CU >= 0) load_x(0);
-    f4 acc[MT][NT];
+    f4 acc[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int m = 0; m < MT; ++m) acc[m] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int kc = 0; kc < nc; ++kc) {
+      __builtin_amdgcn_s_waitcnt(0x0070);      // vmcnt(0) lgkmcnt(0): this wave's rows are in LDS
+      __syncthreads();
+      u4w w[kPairs];
+      w[0] = ws[0][l];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) acc[m][t] = f4{0.f, 0.f, 0.f, 0.f};
-    u4w bq[NP][NT];
-#pragma unroll
-    for (int j = 0; j < D; ++j) load_b(0, j, bq[j]);
-    store_x();
-    __syncthreads();
-    for (int kc = 0; kc < KC; ++kc) {
-#pragma unroll
-      for (int pp = 0; pp < NP; ++pp) {
-        if (pp + D < NP) load_b(kc, pp + D, bq[pp + D]);
-        else if (kc + 1 < KC) load_b(kc + 1, pp + D - NP, bq[pp + D - NP]);
-        if (KC > 1 && pp == NP / 2 && kc + 1 < KC) {
-          if (CU > 0 && kc + 1 == CU) set_offsets(in, g, 0);      // the rest of the input comes from `in`
-          load_x(kc + 1);
-        }
-        // taps 2 pp (lanes 0-31) and 2 pp + 1 (lanes 32-63; tap 27 reads tap 26's input)
-        const int off = second ? tap_off<HY>(2 * pp + 1 < 27 ? 2 * pp + 1 : 26) : tap_off<HY>(2 * pp);
+      for (int p = 0; p < kPairs; ++p) {
+        if (p + 1 < kPairs) w[p + 1] = ws[p + 1][l];
+        // the lane's voxel of row 0 at its tap (27: zero weights on tap 26's input)
+        const int ta = 2 * p, tb = 2 * p + 1 < 27 ? 2 * p + 1 : 26;
+        const int row0 = i + kHX * HY * wave + (second ? tap_off<HY>(tb) : tap_off<HY>(ta));
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
-          const bf8v a =
-              __builtin_bit_cast(bf8v, *reinterpret_cast<const u4w*>(&xs[abase + off + kHX * m][8 * half]));
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-            acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf8v, bq[pp][t]),
-                                                                acc[m][t], 0, 0, 0);
+          const bf8v x = __builtin_bit_cast(bf8v, *reinterpret_cast<const u4w*>(&xs[row0 + kHX * m][8 * half]));
+          acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, w[p]), x, acc[m], 0, 0, 0);
         }
       }
-      if (kc + 1 < KC) {      // next chunk: its input block replaces this one
+      sched_products<MT, 0>();
+      if (MULTI && kc + 1 < nc) {
         __syncthreads();
-        store_x();
-        __syncthreads();
+        if (MODE == 1 && kc + 1 == cu) set_offsets(in, g, 0);      // the rest of the input comes from `in`
+        load(kc + 1);
       }
     }
-    const int oz = z0 + wave, oxb = x0 + 4 * (l >> 4);
-    if (out32) {
-      if (oz < g.Z) {
-        const long long vz = (long long)g.X * g.Y * oz;
+    const bool pool = pout.p != nullptr;
+    if (pool) __syncthreads();         // every wave is done with the input block
+    // lane: channels 16 t0 + 4 (l / 16) + e of voxel (x0 + i, y0 + m, z0 + wave)
+    const int x = o.x + i, z = o.z + wave, q = l >> 4;
+    const long long vz = x + (long long)g.X * (o.y + (long long)g.Y * z);
+    if (out32) {                       // the last layer: two channels in FP32
+      if (q == 0 && x < g.X && z < g.Z) {
+        const float c0 = bias ? bias[0] : 0.f, c1 = bias ? bias[1] : 0.f;
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
-          const int oy = y0 + m;
-          if (oy >= g.Y) continue;
-          const long long vm = vz + (long long)g.X * oy + oxb;
-#pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            const int co = t * 16 + i;
-            if (co >= cout) continue;
-            const float bc = bias ? bias[co] : 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              if (oxb + e >= g.X) continue;
-              float val = acc[m][t][e] + bc;
-              if (relu) val = fmaxf(val, 0.f);
-              out32[(vm + e) * 2 + co] = val;
-            }
+          float v0 = acc[m][0] + c0, v1 = acc[m][1] + c1;
+          if (relu) {
+            v0 = fmaxf(v0, 0.f);
+            v1 = fmaxf(v1, 0.f);
           }
+          if (o.y + m < g.Y) *reinterpret_cast<float2*>(out32 + (vz + (long long)g.X * m) * 2) = make_float2(v0, v1);
         }
       }
       return;
     }
-    // BF16 results of this wave to LDS as [voxel x + 16 m][channel], then 16-byte pieces to memory
-    __syncthreads();                                  // every wave is done with the input block
-    bf16* ost = reinterpret_cast<bf16*>(lds) + wave * (OV * COUTP);
+    bf16* res = &xs[0][0];             // [z][y][x][16] of the block, where it is pooled
+    const int co = 16 * t0 + 4 * q;
+    float b[4] = {0.f, 0.f, 0.f, 0.f};
+    if (bias) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int co = t * 16 + i;
-      const float bc = bias ? bias[co] : 0.f;
-#pragma unroll
-      for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float val = acc[m][t][e] + bc;
-          if (relu) val = fmaxf(val, 0.f);
-          ost[(4 * (l >> 4) + e + 16 * m) * COUTP + co] = f2bf(val);
-        }
+      for (int e = 0; e < 4; ++e) b[e] = bias[co + e];
     }
-    __syncthreads();
-    if (oz < g.Z) {
-      constexpr int C8 = COUTP / 8;
-      const long long vz = (long long)g.X * g.Y * oz;
+    bf16* dst = out.p + vz * out.cs + out.coff + co;
 #pragma unroll
-      for (int k = l; k < OV * C8; k += 64) {
-        const int v = k / C8, c8 = k - v * C8;
-        const int x = x0 + (v & 15), y = y0 + (v >> 4);
-        if (x < g.X && y < g.Y && 8 * c8 < cout)
-          *reinterpret_cast<u4w*>(out.p + (vz + (long long)g.X * y + x) * out.cs + out.coff + 8 * c8) =
-              *reinterpret_cast<const u4w*>(ost + v * COUTP + 8 * c8);
-      }
+    for (int m = 0; m < MT; ++m) {
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = relu ? fmaxf(acc[m][e] + b[e], 0.f) : acc[m][e] + b[e];
+      const u2w w = {unsigned(f2bf(v[0])) | (unsigned(f2bf(v[1])) << 16),
+                     unsigned(f2bf(v[2])) | (unsigned(f2bf(v[3])) << 16)};
+      if (pool) *reinterpret_cast<u2w*>(res + ((wave * MT + m) * 16 + i) * 16 + 4 * q) = w;
+      if (x < g.X && z < g.Z && o.y + m < g.Y) *reinterpret_cast<u2w*>(dst + (long long)g.X * m * out.cs) = w;
     }
     // pout: the 2 x 2 x 2 average pool of the block's results on the half grid
     // gp (blocks are even-aligned; children outside the grid add nothing,
     // divisor 8, children summed z, y, x in FP32 as pool8_kernel does)
-    if (MT % 2 == 0 && pout.p) {
-      constexpr int C8 = COUTP / 8, PY = MT / 2, PV = 8 * PY * 2;
-      const bf16* res = reinterpret_cast<const bf16*>(lds);
-      for (int k = tid; k < PV * C8; k += 256) {
-        const int pv = k / C8, c8 = k - pv * C8;
-        const int px = pv & 7, py = (pv >> 3) % PY, pz = pv / (8 * PY);
-        const int qx = x0 / 2 + px, qy = y0 / 2 + py, qz = z0 / 2 + pz;
-        if (qx >= gp.X || qy >= gp.Y || qz >= gp.Z) continue;
-        float sacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int dz = 0; dz < 2; ++dz)
-          for (int dy = 0; dy < 2; ++dy)
-            for (int dx = 0; dx < 2; ++dx) {
-              const int fx = 2 * px + dx, fy = 2 * py + dy, fz = 2 * pz + dz;
-              if (x0 + fx >= g.X || y0 + fy >= g.Y || z0 + fz >= g.Z) continue;
-              const u4w w = *reinterpret_cast<const u4w*>(res + fz * (OV * COUTP) + (fx + 16 * fy) * COUTP + 8 * c8);
+    if (!pool) return;
+    __syncthreads();
+    constexpr int PY = MT / 2, PV = 8 * PY * 2;
+    for (int k = tid; k < PV * 2; k += 256) {
+      const int pv = k / 2, c8 = k & 1;
+      const int px = pv & 7, py = (pv >> 3) % PY, pz = pv / (8 * PY);
+      const int qx = o.x / 2 + px, qy = o.y / 2 + py, qz = o.z / 2 + pz;
+      if (qx >= gp.X || qy >= gp.Y || qz >= gp.Z) continue;
+      float sacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      for (int dz = 0; dz < 2; ++dz)
+        for (int dy = 0; dy < 2; ++dy)
+          for (int dx = 0; dx < 2; ++dx) {
+            const int fx = 2 * px + dx, fy = 2 * py + dy, fz = 2 * pz + dz;
+            if (o.x + fx >= g.X || o.y + fy >= g.Y || o.z + fz >= g.Z) continue;
+            const u4w w = *reinterpret_cast<const u4w*>(res + ((fz * MT + fy) * 16 + fx) * 16 + 8 * c8);
 #pragma unroll
-              for (int kk = 0; kk < 4; ++kk) {
-                sacc[2 * kk] += bf2f(bf16(w[kk] & 0xffffu));
-                sacc[2 * kk + 1] += bf2f(bf16(w[kk] >> 16));
-              }
+            for (int kk = 0; kk < 4; ++kk) {
+              sacc[2 * kk] += bf2f(bf16(w[kk] & 0xffffu));
+              sacc[2 * kk + 1] += bf2f(bf16(w[kk] >> 16));
             }
-        u4w o;
+          }
+      u4w pk;
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-          o[kk] = unsigned(f2bf(sacc[2 * kk] * 0.125f)) | (unsigned(f2bf(sacc[2 * kk + 1] * 0.125f)) << 16);
-        *reinterpret_cast<u4w*>(pout.p + (qx + (long long)gp.X * (qy + (long long)gp.Y * qz)) * pout.cs +
-                                pout.coff + 8 * c8) = o;
-      }
+      for (int kk = 0; kk < 4; ++kk)
+        pk[kk] = unsigned(f2bf(sacc[2 * kk] * 0.125f)) | (unsigned(f2bf(sacc[2 * kk + 1] * 0.125f)) << 16);
+      *reinterpret_cast<u4w*>(pout.p + (qx + (long long)gp.X * (qy + (long long)gp.Y * qz)) * pout.cs + pout.coff +
+                              16 * t0 + 8 * c8) = pk;
     }
   }
 }
@@ -497,17 +462,25 @@ __global__ __launch_bounds__(kWrW * kWrS) void wgrad_reduce_kernel(const float* 
   if (co < cout && ci < cin) gw[(size_t(co) * cin + ci) * 27 + tap] = t;
 }
 
-// BF16 weight copies of one layer from the FP32 master (parameter layout):
-// fwd[tap][co][ci] (co < coutp, ci < cinp, zero padded) for the forward pass,
-// bwd[tap'][ci][co] = W[co][ci][26 - tap'] for the input gradient.
+// BF16 weight copies of one layer from the FP32 master (parameter layout), in the
+// order in which conv_kernel stages them: [chunk][pair][16 output channels][lane][8],
+// lane l of pair p holding output channel l % 16, channels 8 (l / 16 % 2) .. + 7 of
+// the chunk, tap 2 p + l / 32 (zero for tap 27 and for padded channels).  fwd: input
+// ci, output co; bwd (input gradient): input co, output ci, the taps mirrored.
+__host__ __device__ constexpr int packed_weights(int cinp, int coutp) { return 2 * kPairs * cinp * coutp; }
 __global__ void pack_kernel(const float* __restrict__ w, int cin, int cout, int cinp, int coutp,
                             bf16* __restrict__ fwd, bf16* __restrict__ bwd) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= 27 * coutp * cinp) return;
-  const int ci = idx % cinp, co = (idx / cinp) % coutp, tap = idx / (cinp * coutp);
-  const float val = (ci < cin && co < cout) ? w[((size_t)co * cin + ci) * 27 + tap] : 0.f;
-  fwd[idx] = f2bf(val);
-  bwd[((size_t)(26 - tap) * cinp + ci) * coutp + co] = f2bf(val);
+  if (idx >= packed_weights(cinp, coutp)) return;
+  const int lane = (idx >> 3) & 63, frag = idx >> 9;
+  auto value = [&](int outp, bool back) {
+    const int nt = outp / 16, t = frag % nt, p = frag / nt % kPairs, kc = frag / (nt * kPairs);
+    const int o = 16 * t + (lane & 15), in = 16 * kc + 8 * ((lane >> 4) & 1) + (idx & 7), tap = 2 * p + (lane >> 5);
+    const int co = back ? in : o, ci = back ? o : in;
+    return tap < 27 && ci < cin && co < cout ? w[(size_t(co) * cin + ci) * 27 + (back ? 26 - tap : tap)] : 0.f;
+  };
+  fwd[idx] = f2bf(value(coutp, false));
+  bwd[idx] = f2bf(value(cinp, true));
 }
 
 // network input: (Re r / s, Im r / s, kh, 0 ...) with s^2 = mean |r|^2 (16 channels)
@@ -808,44 +781,42 @@ hipError_t dalloc(h6_net N, T** p, size_t count) {
   return hipMemset(q, 0, count * sizeof(T) + 64);
 }
 
-unsigned nblk(long long n, int b = 256) { return unsigned((n + b - 1) / b); }
+// Workgroups below which a convolution takes blocks of 4 rows instead of 8: two per
+// CU.  Smaller blocks read more halo (48 -> 16 at 128 x 130 x 130: 109 against 98 us),
+// larger ones leave CUs idle (64 -> 64 at 16 x 17 x 17 would run on 36).
+constexpr int kConvBlocks = 512;
 
-#define H6_CONV_CASES(X) \
-  X(16, 16) X(16, 32) X(16, 48) X(48, 16) X(96, 32) X(64, 32) X(32, 32) X(32, 64) X(32, 96) X(32, 16) X(64, 64)
-// decoder layers whose first `cu` input chunks are the upsampled coarser level
-// (cu = -1: the first layer reading the residual's features)
-#define H6_CONV_UP_CASES(X) X(96, 32, 4) X(48, 16, 2) X(16, 16, -1)
+unsigned nblk(long long n, int b = 256) { return unsigned((n + b - 1) / b); }
 
 // out = act(conv(in)); with cu > 0 the first cu 16-channel chunks of the input are
 // the nearest-neighbour upsampling of `up` (grid gu = half(g)) and the rest come from `in`
 // cu < 0: the input is the features of the residual fr (first layer, cinp = 16);
-// pout.p != nullptr (up to 32 output channels): the output's 2 x 2 x 2 average
-// pool also goes to pout on the half grid gp
+// pout.p != nullptr: the output's 2 x 2 x 2 average pool also goes to pout on the
+// half grid gp; out32: two output channels in FP32
 hipError_t conv(View in, int cinp, const bf16* W, int coutp, const float* bias, View out, float* out32,
                 int cout, int relu, Grid3 g, hipStream_t s, View up = View{nullptr, 0, 0}, Grid3 gu = Grid3{0, 0, 0},
                 int cu = 0, const double2* fr = nullptr, const double* fnrm = nullptr, float fkh = 0.f,
                 View pout = View{nullptr, 0, 0}, Grid3 gp = Grid3{0, 0, 0}) {
-  if (pout.p && (conv_rows(coutp) % 2 != 0 || out32)) return hipErrorInvalidValue;
-  const int rows = conv_rows(coutp);
-  const int ntx = (g.X + kTX - 1) / kTX, nty = (g.Y + rows - 1) / rows, ntz = (g.Z + kTZ - 1) / kTZ;
-  const unsigned grid = unsigned(ntx) * nty * ntz;
-#define H6_CONV(CI, CO)                                                                                   \
-  if (cu == 0 && cinp == CI && coutp == CO) {                                                             \
-    hipLaunchKernelGGL((conv_tile_x32_kernel<CI, CO, 0>), dim3(grid), dim3(256), 0, s, in, W, bias, out,  \
-                       out32, cout, relu, g, ntx, nty, up, gu, fr, fnrm, fkh, pout, gp);                  \
-    return hipGetLastError();                                                                             \
-  }
-  H6_CONV_CASES(H6_CONV)
-#undef H6_CONV
-#define H6_CONV_UP(CI, CO, CUP)                                                                             \
-  if (cu == CUP && cinp == CI && coutp == CO) {                                                             \
-    hipLaunchKernelGGL((conv_tile_x32_kernel<CI, CO, CUP>), dim3(grid), dim3(256), 0, s, in, W, bias, out, \
-                       out32, cout, relu, g, ntx, nty, up, gu, fr, fnrm, fkh, pout, gp);                    \
-    return hipGetLastError();                                                                               \
-  }
-  H6_CONV_UP_CASES(H6_CONV_UP)
-#undef H6_CONV_UP
-  return hipErrorInvalidValue;
+  if (cinp % 16 || coutp % 16 || cu >= cinp / 16 || (cu < 0 && cinp != 16)) return hipErrorInvalidValue;
+  if (out32 ? cout != 2 || coutp != 16 || pout.p : cout != coutp) return hipErrorInvalidValue;
+  const int ntx = (g.X + kTX - 1) / kTX, ntz = (g.Z + kTZ - 1) / kTZ, ntall = coutp / 16, chunks = cinp / 16;
+  auto rows = [&](int mt) { return (g.Y + mt - 1) / mt; };
+  const int mt = ntx * rows(8) * ntz * ntall < kConvBlocks ? 4 : 8;
+  const int nblocks = ntx * rows(mt) * ntz;
+  auto go = [&](auto MT, auto MODE, auto MULTI) {
+    hipLaunchKernelGGL((conv_kernel<MT(), MODE(), MULTI()>), dim3(nblocks * ntall), dim3(256), 0, s, in, W, bias, out,
+                       out32, chunks, ntall, relu, g, ntx, rows(mt), up, gu, cu, fr, fnrm, fkh, pout, gp);
+    return hipGetLastError();
+  };
+  auto mode = [&](auto MT) {
+    constexpr std::integral_constant<int, 0> plain{};
+    constexpr std::integral_constant<int, 1> upsampled{};
+    constexpr std::integral_constant<int, 2> features{};
+    if (cu < 0) return go(MT, features, std::false_type{});
+    if (cu > 0) return go(MT, upsampled, std::true_type{});
+    return chunks > 1 ? go(MT, plain, std::true_type{}) : go(MT, plain, std::false_type{});
+  };
+  return mt == 8 ? mode(std::integral_constant<int, 8>{}) : mode(std::integral_constant<int, 4>{});
 }
 
 // Partial rows of a layer with coutp x cinp channels: about kWgRows workgroups,
@@ -1003,7 +974,7 @@ hipError_t backward(h6_net N, hipStream_t s) {
 hipError_t pack_all(h6_net N, hipStream_t s) {
   for (int L = 0; L < NL; ++L) {
     const LayerDef& d = kLayers[L];
-    const int n = 27 * r16(d.cout) * r16(d.cin);
+    const int n = packed_weights(r16(d.cin), r16(d.cout));
     hipLaunchKernelGGL(pack_kernel, dim3(nblk(n)), dim3(256), 0, s, N->w32 + N->off[L], d.cin, d.cout,
                        r16(d.cin), r16(d.cout), N->wf[L], N->wb[L]);
   }
@@ -1105,7 +1076,7 @@ h6_status h6net_create(const int dims[3], void* hip_stream, h6_net* out) {
   if (e == hipSuccess) e = dalloc(N, &N->w32, size_t(N->np));
   if (e == hipSuccess) e = dalloc(N, &N->grad, size_t(N->np));
   for (int L = 0; L < NL && e == hipSuccess; ++L) {
-    const size_t n = size_t(27) * r16(kLayers[L].cout) * r16(kLayers[L].cin);
+    const size_t n = packed_weights(r16(kLayers[L].cin), r16(kLayers[L].cout));
     e = dalloc(N, &N->wf[L], n);
     if (e == hipSuccess) e = dalloc(N, &N->wb[L], n);
   }
