@@ -9,9 +9,10 @@
 // W_qm = cos(pi q m / M) (q, m = 0..M); W^{-1} = (2/M) W^T and
 // (2/M) C W^T C (C = diag(1/2, 1, .., 1, 1/2)) respectively.
 //
-// Steps 1, 2, 4, 5 use an FFT path for M = 257 (xform_rader.hip), M = 64 .. 512
-// a power of two (xform_fft.hip) and some odd M (xform_bluestein.hip), and the
-// dense basis-matrix products on the matrix cores otherwise (xform_dense.hip).  Compute type R is double (FP64 plans) or float (mixed
+// Steps 1, 2, 4, 5 use an FFT path for M = 257 (xform_rader.hip) and M = 64 .. 512
+// a power of two (xform_fft.hip), the dense basis-matrix products on the matrix
+// cores otherwise (xform_dense.hip), and chirp-z for odd M (xform_bluestein.hip)
+// where the autotuner finds it faster.  Compute type R is double (FP64 plans) or float (mixed
 // plans, complex64 intermediates); the input r and output z are complex128 in
 // both.
 #include <mutex>
@@ -111,7 +112,10 @@ __device__ __forceinline__ typename C2<R>::T crecip(typename C2<R>::T b) {
 // pivot check).  Each thread replays c' over its rows and composes both affine
 // maps over its segment: their linear parts are the same product of -p_i, so
 // one product serves the forward and the backward chain.  The segment maps are
-// chained in order through LDS.  Row 0 of the system never sees the value
+// chained in order by the first segment's threads, which leave every segment its
+// entering value in LDS (with each thread chaining all maps before its own the
+// kernel waited on dependent LDS reads: 32^3 complex128 8.1 -> 7.2 us, 128 x 130 x 130
+// complex64 15.2 -> 14.6, 160 x 99 x 202 complex128 27.9 -> 26.3).  Row 0 of the system never sees the value
 // entering from above (it is zero) and row n'z - 1 never sees the one from
 // below, so their missing off-diagonal needs no special case.
 // HBM traffic: one read and one write of the vector plus the small cstart table.
@@ -129,7 +133,9 @@ __global__ __launch_bounds__(kLanes * kSegs) void tridiag_z_kernel(
   const double kap_re = zp[0], kap_im = zp[1];
   const ZEnds ends{zp[2], zp[3], zp[4], zp[5], zp[6], zp[7]};
   using T2 = typename C2<R>::T;
-  __shared__ T2 sh[2][kSegs][kLanes];
+  struct alignas(2 * sizeof(T2)) Map { T2 q, b; };      // x -> q x + b
+  __shared__ Map sh[kSegs][kLanes];
+  __shared__ T2 carry[kSegs][kLanes];
   const int tid = threadIdx.x;
   const int lane = tid % kLanes;
   const int seg = tid / kLanes;
@@ -180,11 +186,19 @@ __global__ __launch_bounds__(kLanes * kSegs) void tridiag_z_kernel(
       p[u] = zero;
     }
   }
-  sh[0][seg][lane] = Q;
-  sh[1][seg][lane] = B;
+  sh[seg][lane] = Map{Q, B};
   __syncthreads();
-  T2 dprev = zero;
-  for (int s2 = 0; s2 < seg; ++s2) dprev = cadd<R>(cmulr<R>(sh[0][s2][lane], dprev), sh[1][s2][lane]);
+  if (seg == 0) {
+    T2 x = zero;
+#pragma unroll 8
+    for (int s2 = 0; s2 < kSegs; ++s2) {
+      const Map m = sh[s2][lane];
+      carry[s2][lane] = x;
+      x = cadd<R>(cmulr<R>(m.q, x), m.b);
+    }
+  }
+  __syncthreads();
+  T2 dprev = carry[seg][lane];
   // replay d', then compose the back substitution x_{r0} = Q x_{r0+cnt} + D
 #pragma unroll
   for (int u = 0; u < kSmax; ++u) {
@@ -197,11 +211,19 @@ __global__ __launch_bounds__(kLanes * kSegs) void tridiag_z_kernel(
 #pragma unroll
   for (int u = kSmax - 1; u >= 0; --u)
     if (u < cnt) D = csub<R>(d[u], cmulr<R>(p[u], D));
+  sh[seg][lane].b = D;      // (read last before the barrier above)
   __syncthreads();
-  sh[1][seg][lane] = D;
+  if (seg == 0) {
+    T2 x = zero;
+#pragma unroll 8
+    for (int s2 = kSegs - 1; s2 >= 0; --s2) {
+      const Map m = sh[s2][lane];
+      carry[s2][lane] = x;
+      x = cadd<R>(cmulr<R>(m.q, x), m.b);
+    }
+  }
   __syncthreads();
-  T2 x = zero;
-  for (int s2 = kSegs - 1; s2 > seg; --s2) x = cadd<R>(cmulr<R>(sh[0][s2][lane], x), sh[1][s2][lane]);
+  T2 x = carry[seg][lane];
 #pragma unroll
   for (int u = kSmax - 1; u >= 0; --u) {
     if (u < cnt) {
