@@ -563,10 +563,14 @@ h6_status setup_impl(const h6_params* p, hipStream_t s, h6_plan* out, std::strin
     if (P->ax[a].M == kRaderM && !std::getenv("H6_DENSE_TRANSFORMS")) e = build_rader(P->ax[a], s);
     else if (bluestein_ok(P->ax[a].M) && P->ax[a].L <= 256 && !std::getenv("H6_DENSE_TRANSFORMS")) {
       e = build_bluestein(P->ax[a], s);
-      // (untuned plans take the dense product: since its slab kernels it is faster for
-      // every odd M, also where the chirp-z length is all signal, and no less exact.
-      // apply_Pinv, chirp-z against dense: 128^3 complex64 107 -> 82 us, complex128 155
-      // -> 117; 254 x 254 x 160 577 -> 381, 1052 -> 644; the autotuner times both)
+      // Untuned plans take the dense product: since its slab kernels it is faster for
+      // every odd M, also where the chirp-z length is nearly all signal (2M - 2 >=
+      // 15/16 P), and no less exact.  apply_Pinv, chirp-z against dense: 128^3 complex64
+      // 107 -> 82 us, complex128 155 -> 117; 254 x 254 x 160 577 -> 381, 1052 -> 644.  Only
+      // grids of fewer lines than one slab keep the chirp-z path there (128 x 2 x 2: 26
+      // against 18 us), so that what they return, bit for bit, stays as it was.
+      const int M = P->ax[a].M, lines = P->dims[1 - a] * P->dims[2];
+      if (e == hipSuccess && 16 * (2 * M - 2) >= 15 * bluestein_length(M) && lines < 16) P->ax[a].fast = 2;
     }
     else if (fft_ok(P->ax[a].M) && !std::getenv("H6_DENSE_TRANSFORMS")) {
       e = build_fft(P->ax[a], s);
