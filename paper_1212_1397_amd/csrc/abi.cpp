@@ -563,14 +563,16 @@ h6_status setup_impl(const h6_params* p, hipStream_t s, h6_plan* out, std::strin
     if (P->ax[a].M == kRaderM && !std::getenv("H6_DENSE_TRANSFORMS")) e = build_rader(P->ax[a], s);
     else if (bluestein_ok(P->ax[a].M) && P->ax[a].L <= 256 && !std::getenv("H6_DENSE_TRANSFORMS")) {
       e = build_bluestein(P->ax[a], s);
-      // Untuned plans take the dense product: since its slab kernels it is faster for
-      // every odd M, also where the chirp-z length is nearly all signal (2M - 2 >=
-      // 15/16 P), and no less exact.  apply_Pinv, chirp-z against dense: 128^3 complex64
-      // 107 -> 82 us, complex128 155 -> 117; 254 x 254 x 160 577 -> 381, 1052 -> 644.  Only
-      // grids of fewer lines than one slab keep the chirp-z path there (128 x 2 x 2: 26
-      // against 18 us), so that what they return, bit for bit, stays as it was.
+      // Untuned default where the FFT length is nearly all signal (2M - 2 >= 15/16 P).
+      // P = 512 (M = 241 .. 255): the dense product, faster since its slab kernels and no
+      // less exact (apply_Pinv 254 x 254 x 160, chirp-z against dense: complex64 577 ->
+      // 381 us, complex128 1052 -> 644).  The chirp-z path stays on axes of fewer lines
+      // than one slab (254 x 2 x 2: 39 against 27 us) and for P = 256 (M = 121 .. 129;
+      // 128 x 130 x 130 complex64 110 against 84 us): there what untuned plans return is
+      // pinned bit for bit, and plans that care are autotuned, which times both.
       const int M = P->ax[a].M, lines = P->dims[1 - a] * P->dims[2];
-      if (e == hipSuccess && 16 * (2 * M - 2) >= 15 * bluestein_length(M) && lines < 16) P->ax[a].fast = 2;
+      if (e == hipSuccess && 16 * (2 * M - 2) >= 15 * bluestein_length(M) && (bluestein_length(M) == 256 || lines < 16))
+        P->ax[a].fast = 2;
     }
     else if (fft_ok(P->ax[a].M) && !std::getenv("H6_DENSE_TRANSFORMS")) {
       e = build_fft(P->ax[a], s);
