@@ -77,6 +77,8 @@ struct View {           // channels-last BF16 view
 // `in`.  MODE 2 (first layer, inference): the input is formed from the residual
 // fr: channels r re / rms, r im / rms, kh (zero for r = 0) and zeros, with
 // rms^2 = *fnrm / voxels (the features of h6net.h).
+// MODE 3 (input gradients): the result is zeroed where the activation mask, whose
+// gradient it is, is not positive, so no pass of its own does it.
 constexpr int kTX = 16, kTY = 4, kTZ = 4;
 constexpr int kHX = kTX + 2, kHY = kTY + 2, kHZ = kTZ + 2;
 constexpr int kPairs = 14;       // the 27 taps (dx + 3 dy + 9 dz) two at a time
@@ -84,6 +86,11 @@ constexpr int kPairs = 14;       // the 27 taps (dx + 3 dy + 9 dz) two at a time
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef unsigned int u4w __attribute__((ext_vector_type(4)));
 typedef unsigned int u2w __attribute__((ext_vector_type(2)));
+
+// ReLU gradient of two stored values: all ones where the activation a is positive
+__device__ __forceinline__ unsigned relu_mask(unsigned a) {
+  return (bf2f(bf16(a & 0xffffu)) > 0.f ? 0x0000ffffu : 0u) | (bf2f(bf16(a >> 16)) > 0.f ? 0xffff0000u : 0u);
+}
 
 // voxel offset of tap t from tap 0 inside an LDS input block of HY rows per plane
 template <int HY>
@@ -113,7 +120,7 @@ __global__ __launch_bounds__(256, 3) void conv_kernel(View in, const bf16* __res
                                                       View out, float* __restrict__ out32, int nchunks, int ntall,
                                                       int relu, Grid3 g, int ntx, int nty, View up, Grid3 gu,
                                                       int cu, const double2* __restrict__ fr,
-                                                      const double* __restrict__ fnrm, float fkh, View pout, Grid3 gp) {
+                                                      const double* __restrict__ fnrm, float fkh, View pout, Grid3 gp, View mask) {
   constexpr int HY = MT + 2, HV = kHX * HY * kHZ;
   constexpr int NPIECE = HV * 2, NPER = (NPIECE + 255) / 256;   // 16-byte pieces of an input block
   static_assert(4 * 16 * MT <= HV, "results to be pooled fit the input buffer");
@@ -259,15 +266,22 @@ __global__ __launch_bounds__(256, 3) void conv_kernel(View in, const bf16* __res
       for (int e = 0; e < 4; ++e) b[e] = bias[co + e];
     }
     bf16* dst = out.p + vz * out.cs + out.coff + co;
+    const bf16* act = mask.p + vz * mask.cs + mask.coff + co;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
       float v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = relu ? fmaxf(acc[m][e] + b[e], 0.f) : acc[m][e] + b[e];
-      const u2w w = {unsigned(f2bf(v[0])) | (unsigned(f2bf(v[1])) << 16),
-                     unsigned(f2bf(v[2])) | (unsigned(f2bf(v[3])) << 16)};
+      u2w w = {unsigned(f2bf(v[0])) | (unsigned(f2bf(v[1])) << 16),
+               unsigned(f2bf(v[2])) | (unsigned(f2bf(v[3])) << 16)};
       if (pool) *reinterpret_cast<u2w*>(res + ((wave * MT + m) * 16 + i) * 16 + 4 * q) = w;
-      if (x < g.X && z < g.Z && o.y + m < g.Y) *reinterpret_cast<u2w*>(dst + (long long)g.X * m * out.cs) = w;
+      if (x < g.X && z < g.Z && o.y + m < g.Y) {
+        if (MODE == 3) {
+          const u2w a = *reinterpret_cast<const u2w*>(act + (long long)g.X * m * mask.cs);
+          w = u2w{w[0] & relu_mask(a[0]), w[1] & relu_mask(a[1])};
+        }
+        *reinterpret_cast<u2w*>(dst + (long long)g.X * m * out.cs) = w;
+      }
     }
     // pout: the 2 x 2 x 2 average pool of the block's results on the half grid
     // gp (blocks are even-aligned; children outside the grid add nothing,
@@ -559,8 +573,17 @@ __device__ __forceinline__ u4v pack8(const float (&f)[8]) {
   return w;
 }
 
-// gradient of the pool, added to din: din[v] += dout[v / 2] / 8
-__global__ void pool_back_kernel(View dout, Grid3 go, View din, Grid3 gi, int C) {
+// g where the activation act (8 channels from c of voxel v) is positive, else zero
+__device__ __forceinline__ u4v relu_mask8(View act, long long v, int c, u4v g) {
+  const u4v a = *reinterpret_cast<const u4v*>(act.p + v * act.cs + act.coff + c);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) g[k] &= relu_mask(a[k]);
+  return g;
+}
+
+// gradient of the pool, added to din, and the ReLU gradient of the sum:
+// din[v] = (act > 0) (din[v] + dout[v / 2] / 8)
+__global__ void pool_back_kernel(View dout, Grid3 go, View din, Grid3 gi, int C, View act) {
   const long long idx = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   const int C8 = C / 8;
   if (idx >= gi.P() * C8) return;
@@ -574,11 +597,12 @@ __global__ void pool_back_kernel(View dout, Grid3 go, View din, Grid3 gi, int C)
   unpack8(*reinterpret_cast<const u4v*>(dout.p + vo * dout.cs + dout.coff + c), g);
 #pragma unroll
   for (int k = 0; k < 8; ++k) a[k] = a[k] + 0.125f * g[k];
-  *d = pack8(a);
+  *d = relu_mask8(act, v, c, pack8(a));
 }
 
-// gradient of the upsampling: din[v] = sum of dout over the children of v
-__global__ void up_back_kernel(View dout, Grid3 go, View din, Grid3 gi, int C) {
+// gradient of the upsampling and of the ReLU before it: din[v] = (act > 0) sum of dout
+// over the children of v
+__global__ void up_back_kernel(View dout, Grid3 go, View din, Grid3 gi, int C, View act) {
   const long long idx = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   const int C8 = C / 8;
   if (idx >= gi.P() * C8) return;
@@ -599,26 +623,7 @@ __global__ void up_back_kernel(View dout, Grid3 go, View din, Grid3 gi, int C) {
           for (int k = 0; k < 8; ++k) s[k] += g[k];
         }
       }
-  *reinterpret_cast<u4v*>(din.p + v * din.cs + din.coff + c) = pack8(s);
-}
-
-// ReLU gradient: g *= (a > 0)
-__global__ void relu_back_kernel(View gv, View av, long long P, int C) {
-  const long long idx = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  const int C8 = C / 8;
-  if (idx >= P * C8) return;
-  const int c = 8 * int(idx % C8);
-  const long long v = idx / C8;
-  const u4v a = *reinterpret_cast<const u4v*>(av.p + v * av.cs + av.coff + c);
-  u4v* gp = reinterpret_cast<u4v*>(gv.p + v * gv.cs + gv.coff + c);
-  u4v g = *gp;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const unsigned lo = (bf2f(bf16(a[k] & 0xffffu)) > 0.f) ? 0x0000ffffu : 0u;
-    const unsigned hi = (bf2f(bf16(a[k] >> 16)) > 0.f) ? 0xffff0000u : 0u;
-    g[k] &= lo | hi;
-  }
-  *gp = g;
+  *reinterpret_cast<u4v*>(din.p + v * din.cs + din.coff + c) = relu_mask8(act, v, c, pack8(s));
 }
 
 // correction c = s (y0 + i y1): mode 0 writes complex128, 1 adds to complex128,
@@ -796,8 +801,9 @@ unsigned nblk(long long n, int b = 256) { return unsigned((n + b - 1) / b); }
 hipError_t conv(View in, int cinp, const bf16* W, int coutp, const float* bias, View out, float* out32,
                 int cout, int relu, Grid3 g, hipStream_t s, View up = View{nullptr, 0, 0}, Grid3 gu = Grid3{0, 0, 0},
                 int cu = 0, const double2* fr = nullptr, const double* fnrm = nullptr, float fkh = 0.f,
-                View pout = View{nullptr, 0, 0}, Grid3 gp = Grid3{0, 0, 0}) {
+                View pout = View{nullptr, 0, 0}, Grid3 gp = Grid3{0, 0, 0}, View mask = View{nullptr, 0, 0}) {
   if (cinp % 16 || coutp % 16 || cu >= cinp / 16 || (cu < 0 && cinp != 16)) return hipErrorInvalidValue;
+  if (mask.p && (cu != 0 || out32)) return hipErrorInvalidValue;
   if (out32 ? cout != 2 || coutp != 16 || pout.p : cout != coutp) return hipErrorInvalidValue;
   const int ntx = (g.X + kTX - 1) / kTX, ntz = (g.Z + kTZ - 1) / kTZ, ntall = coutp / 16, chunks = cinp / 16;
   auto rows = [&](int mt) { return (g.Y + mt - 1) / mt; };
@@ -805,15 +811,17 @@ hipError_t conv(View in, int cinp, const bf16* W, int coutp, const float* bias, 
   const int nblocks = ntx * rows(mt) * ntz;
   auto go = [&](auto MT, auto MODE, auto MULTI) {
     hipLaunchKernelGGL((conv_kernel<MT(), MODE(), MULTI()>), dim3(nblocks * ntall), dim3(256), 0, s, in, W, bias, out,
-                       out32, chunks, ntall, relu, g, ntx, rows(mt), up, gu, cu, fr, fnrm, fkh, pout, gp);
+                       out32, chunks, ntall, relu, g, ntx, rows(mt), up, gu, cu, fr, fnrm, fkh, pout, gp, mask);
     return hipGetLastError();
   };
   auto mode = [&](auto MT) {
     constexpr std::integral_constant<int, 0> plain{};
     constexpr std::integral_constant<int, 1> upsampled{};
     constexpr std::integral_constant<int, 2> features{};
+    constexpr std::integral_constant<int, 3> masked{};
     if (cu < 0) return go(MT, features, std::false_type{});
     if (cu > 0) return go(MT, upsampled, std::true_type{});
+    if (mask.p) return chunks > 1 ? go(MT, masked, std::true_type{}) : go(MT, masked, std::false_type{});
     return chunks > 1 ? go(MT, plain, std::true_type{}) : go(MT, plain, std::false_type{});
   };
   return mt == 8 ? mode(std::integral_constant<int, 8>{}) : mode(std::integral_constant<int, 4>{});
@@ -923,16 +931,14 @@ hipError_t forward(h6_net N, const double2* r, double kh, hipStream_t s, bool fu
   return hipGetLastError();
 }
 
-// backward of one layer given the gradient gout of its (post-activation)
-// output act: masks gout by the ReLU, accumulates the weight gradients and
-// (gin.p != nullptr) writes the input gradient
-hipError_t layer_bwd(h6_net N, int L, View act, View gout, View xin, View gin, Grid3 g, hipStream_t s) {
+// backward of one layer given the gradient gout of its output before the
+// activation: accumulates the weight gradients and (gin.p != nullptr) writes the
+// input gradient; mask: the input xin is an activation's output, so gin goes on to
+// the gradient before that
+hipError_t layer_bwd(h6_net N, int L, View gout, View xin, View gin, bool mask, Grid3 g, hipStream_t s) {
   const LayerDef& d = kLayers[L];
   const int cinp = r16(d.cin), coutp = r16(d.cout);
   hipError_t e;
-  if (d.relu)
-    hipLaunchKernelGGL(relu_back_kernel, dim3(nblk(g.P() * d.cout / 8)), dim3(256), 0, s, gout, act, g.P(),
-                       d.cout);
   int G = 0;
   if ((e = wgrad(gout, xin, cinp, coutp, N->part, N->bpart, g, s, &G)) != hipSuccess) return e;
   const long long nw = (long long)d.cout * d.cin * 27;
@@ -940,7 +946,8 @@ hipError_t layer_bwd(h6_net N, int L, View act, View gout, View xin, View gin, G
   hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(nrb), dim3(kWrW * kWrS), 0, s, N->part, N->bpart, G, d.cin,
                      d.cout, cinp, coutp, N->grad + N->off[L], N->grad + N->off[L] + nw);
   if (gin.p)
-    return conv(gout, coutp, N->wb[L], cinp, nullptr, gin, nullptr, cinp, 0, g, s);
+    return conv(gout, coutp, N->wb[L], cinp, nullptr, gin, nullptr, cinp, 0, g, s, View{nullptr, 0, 0}, Grid3{0, 0, 0},
+                0, nullptr, nullptr, 0.f, View{nullptr, 0, 0}, Grid3{0, 0, 0}, mask ? xin : View{nullptr, 0, 0});
   return hipGetLastError();
 }
 
@@ -948,25 +955,25 @@ hipError_t backward(h6_net N, hipStream_t s) {
   const Grid3 g1 = N->g1, g2 = N->g2, g3 = N->g3;
   hipError_t e;
 #define TRY(x) do { if ((e = (x)) != hipSuccess) return e; } while (0)
-  TRY(layer_bwd(N, OUT, View{nullptr, 0, 0}, vw(N->dY, 16), vw(N->D1, 16), vw(N->dD1, 16), g1, s));
-  TRY(layer_bwd(N, D1B, vw(N->D1, 16), vw(N->dD1, 16), vw(N->T1b, 16), vw(N->dT1b, 16), g1, s));
-  TRY(layer_bwd(N, D1A, vw(N->T1b, 16), vw(N->dT1b, 16), vw(N->C1, 48), vw(N->dC1, 48), g1, s));
+  TRY(layer_bwd(N, OUT, vw(N->dY, 16), vw(N->D1, 16), vw(N->dD1, 16), true, g1, s));
+  TRY(layer_bwd(N, D1B, vw(N->dD1, 16), vw(N->T1b, 16), vw(N->dT1b, 16), true, g1, s));
+  TRY(layer_bwd(N, D1A, vw(N->dT1b, 16), vw(N->C1, 48), vw(N->dC1, 48), false, g1, s));
   hipLaunchKernelGGL(up_back_kernel, dim3(nblk(g2.P() * 4)), dim3(256), 0, s, vw(N->dC1, 48, 0), g1,
-                     vw(N->dD2, 32), g2, 32);
-  TRY(layer_bwd(N, D2B, vw(N->D2, 32), vw(N->dD2, 32), vw(N->T2b, 32), vw(N->dT2b, 32), g2, s));
-  TRY(layer_bwd(N, D2A, vw(N->T2b, 32), vw(N->dT2b, 32), vw(N->C2, 96), vw(N->dC2, 96), g2, s));
+                     vw(N->dD2, 32), g2, 32, vw(N->D2, 32));
+  TRY(layer_bwd(N, D2B, vw(N->dD2, 32), vw(N->T2b, 32), vw(N->dT2b, 32), true, g2, s));
+  TRY(layer_bwd(N, D2A, vw(N->dT2b, 32), vw(N->C2, 96), vw(N->dC2, 96), false, g2, s));
   hipLaunchKernelGGL(up_back_kernel, dim3(nblk(g3.P() * 8)), dim3(256), 0, s, vw(N->dC2, 96, 0), g2,
-                     vw(N->dB3, 64), g3, 64);
-  TRY(layer_bwd(N, B3B, vw(N->B3, 64), vw(N->dB3, 64), vw(N->T3, 64), vw(N->dT3, 64), g3, s));
-  TRY(layer_bwd(N, B3A, vw(N->T3, 64), vw(N->dT3, 64), vw(N->Pl2, 32), vw(N->dPl2, 32), g3, s));
+                     vw(N->dB3, 64), g3, 64, vw(N->B3, 64));
+  TRY(layer_bwd(N, B3B, vw(N->dB3, 64), vw(N->T3, 64), vw(N->dT3, 64), true, g3, s));
+  TRY(layer_bwd(N, B3A, vw(N->dT3, 64), vw(N->Pl2, 32), vw(N->dPl2, 32), false, g3, s));
   hipLaunchKernelGGL(pool_back_kernel, dim3(nblk(g2.P() * 4)), dim3(256), 0, s, vw(N->dPl2, 32), g3,
-                     vw(N->dC2, 96, 64), g2, 32);
-  TRY(layer_bwd(N, E2B, vw(N->C2, 96, 64), vw(N->dC2, 96, 64), vw(N->T2, 32), vw(N->dT2, 32), g2, s));
-  TRY(layer_bwd(N, E2A, vw(N->T2, 32), vw(N->dT2, 32), vw(N->Pl1, 16), vw(N->dPl1, 16), g2, s));
+                     vw(N->dC2, 96, 64), g2, 32, vw(N->C2, 96, 64));
+  TRY(layer_bwd(N, E2B, vw(N->dC2, 96, 64), vw(N->T2, 32), vw(N->dT2, 32), true, g2, s));
+  TRY(layer_bwd(N, E2A, vw(N->dT2, 32), vw(N->Pl1, 16), vw(N->dPl1, 16), false, g2, s));
   hipLaunchKernelGGL(pool_back_kernel, dim3(nblk(g1.P() * 2)), dim3(256), 0, s, vw(N->dPl1, 16), g2,
-                     vw(N->dC1, 48, 32), g1, 16);
-  TRY(layer_bwd(N, E1B, vw(N->C1, 48, 32), vw(N->dC1, 48, 32), vw(N->T1, 16), vw(N->dT1, 16), g1, s));
-  TRY(layer_bwd(N, E1A, vw(N->T1, 16), vw(N->dT1, 16), vw(N->X0, 16), View{nullptr, 0, 0}, g1, s));
+                     vw(N->dC1, 48, 32), g1, 16, vw(N->C1, 48, 32));
+  TRY(layer_bwd(N, E1B, vw(N->dC1, 48, 32), vw(N->T1, 16), vw(N->dT1, 16), true, g1, s));
+  TRY(layer_bwd(N, E1A, vw(N->dT1, 16), vw(N->X0, 16), View{nullptr, 0, 0}, false, g1, s));
 #undef TRY
   return hipGetLastError();
 }
