@@ -1,4 +1,5 @@
-// Device helpers of the line transforms (xform_rader.hip, xform_bluestein.hip):
+// Device helpers of the line transforms (xform_rader.hip, xform_bluestein.hip,
+// xform_fft.hip):
 // complex arithmetic on float2 / double2 and an in-register FFT of length 16.
 #pragma once
 
@@ -37,6 +38,13 @@ __device__ __forceinline__ typename V2<R>::T mul(typename V2<R>::T a, typename V
 }
 template <typename R>
 __device__ __forceinline__ typename V2<R>::T scl(typename V2<R>::T a, R s) { return mk2<R>(a.x * s, a.y * s); }
+
+// LDS ordering between the lanes of one wave (its LDS accesses are executed in
+// order; the compiler must keep them in order too)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 // radix-4 butterfly; forward uses w4 = -i, inverse w4 = +i
 template <typename R, bool INV>

@@ -105,8 +105,34 @@ __global__ __launch_bounds__(KL * 16) void bluestein_kernel(const Tin* __restric
   __shared__ T2 buf[KL][S::kStride];
   const int M = tab.M;
   const int tid = threadIdx.x;
+  // The tables that every line of the workgroup reads, in LDS for P = 256: about a
+  // hundred gathered loads per thread kept the vector memory path busier than
+  // the lines themselves.  Twiddles as [k][t] = exp(-2 pi i t k / P).  128 x 130 x 130
+  // complex64 y 27.4 -> 21.1 us (cosine inverse), x 22.8 -> 21.8.  Not for complex128 x
+  // lines, which need more workgroups per CU than the larger ones leave (apply_Pinv
+  // 122^3 150 against 144 us).
+  constexpr bool LT = P == 256 && (sizeof(R) == 4 || AXIS == 1);
+  constexpr int NT = LT ? P : 1, NM = LT ? P / 2 + 1 : 1;
+  __shared__ T2 s_tw[NT], s_bhat[NT], s_chirp[NM];
+  __shared__ R s_sin[NM], s_cos[NM];
+  if (LT) {
+    for (int i = tid; i < P; i += KL * 16) {
+      s_tw[i] = tb_tw<R>(tab, (i >> 4) * (i & 15));
+      s_bhat[i] = tb_bhat<R>(tab, i);
+    }
+    for (int i = tid; i < M; i += KL * 16) {
+      s_chirp[i] = tb_chirp<R>(tab, i);
+      s_sin[i] = tb_sin<R>(tab, i);
+      s_cos[i] = tb_cos<R>(tab, i);
+    }
+  }
+  auto twiddle = [&](int t, int k) { return LT ? s_tw[16 * k + t] : tb_tw<R>(tab, t * k); };
+  auto bhat = [&](int i) { return LT ? s_bhat[i] : tb_bhat<R>(tab, i); };
+  auto chirp = [&](int i) { return LT ? s_chirp[i] : tb_chirp<R>(tab, i); };
   const int g = tid >> 4, t = tid & 15;
-  constexpr int kPx = (256 + KL * 16 - 1) / (KL * 16);      // loads per x line (L <= 256)
+  // x lines are loaded and stored by their own wave (WL lines), y columns by the workgroup
+  constexpr int WL = KL < 4 ? KL : 4, kPx = ((LT ? P / 2 + 2 : 256) + 63) / 64;      // loads per x line (L <= M + 1)
+  const int w0 = tid / 64 * 4, wt = tid & 63;
   int nl;
   size_t gbase;
   const int line0 = blockIdx.x * KL;
@@ -114,31 +140,27 @@ __global__ __launch_bounds__(KL * 16) void bluestein_kernel(const Tin* __restric
   if (AXIS == 0) {
     nl = min(KL, nlines - line0);
     gbase = size_t(line0) * L;
-    T2 r[KL][kPx];
+    T2 r[WL][kPx];
 #pragma unroll
-    for (int b = 0; b < KL; ++b)
+    for (int b = 0; b < WL; ++b)
 #pragma unroll
-      for (int k = 0; k < kPx; ++k) {
-        const int p = tid + k * KL * 16;
-        if (b < nl && p < L) r[b][k] = cv<T2>(in[gbase + size_t(b) * L + p]);
-      }
+      for (int k = 0; k < kPx; ++k)
+        r[b][k] = cv<T2>(in[gbase + size_t(min(w0 + b, nl - 1)) * L + min(wt + 64 * k, L - 1)]);
 #pragma unroll
-    for (int b = 0; b < KL; ++b)
+    for (int b = 0; b < WL; ++b)
 #pragma unroll
-      for (int k = 0; k < kPx; ++k) {
-        const int p = tid + k * KL * 16;
-        if (b < nl && p < L) buf[b][p] = r[b][k];
-      }
+      for (int k = 0; k < kPx; ++k)
+        if (wt + 64 * k < L) buf[w0 + b][wt + 64 * k] = r[b][k];
   } else {
     nl = min(KL, nx - line0);
     gbase = size_t(blockIdx.y) * nx * L + line0;
-    constexpr int kPer = (KL * 256 + KL * 16 - 1) / (KL * 16);
+    constexpr int kPer = LT ? (P / 2 + 2 + 15) / 16 : 16;      // rows per thread (L <= M + 1)
     T2 r[kPer];
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
       const int e = tid + k * KL * 16;
       const int q = e / KL, b = e - q * KL;
-      if (q < L && b < nl) r[k] = cv<T2>(in[gbase + size_t(q) * nx + b]);
+      r[k] = cv<T2>(in[gbase + size_t(min(q, L - 1)) * nx + min(b, nl - 1)]);
     }
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
@@ -147,7 +169,8 @@ __global__ __launch_bounds__(KL * 16) void bluestein_kernel(const Tin* __restric
       if (q < L && b < nl) buf[b][q] = r[k];
     }
   }
-  __syncthreads();
+  if (LT || AXIS == 1) __syncthreads();
+  else wave_sync();
 
   // ---- a_q = y_q c_q for q = t + 16 n2 (zero for q = 0 and q >= M) ----
   const int off = NEU ? 0 : -1;                             // array index of node q: q (cosine), q - 1 (sine)
@@ -168,15 +191,15 @@ __global__ __launch_bounds__(KL * 16) void bluestein_kernel(const Tin* __restric
     if (q >= 1 && q < M) {
       const T2 xq = buf[g][q + off], xr = buf[g][M - q + off];
       const T2 s = add<R>(xq, xr), d = sub<R>(xq, xr);
-      const R sn = tb_sin<R>(tab, q);
+      const R sn = (LT ? s_sin[LT ? q : 0] : tb_sin<R>(tab, q));
       T2 y;
       if (NEU) {
         y = add<R>(s, scl<R>(d, sn));
-        c1sum = add<R>(c1sum, scl<R>(d, R(0.5) * tb_cos<R>(tab, q)));
+        c1sum = add<R>(c1sum, scl<R>(d, R(0.5) * (LT ? s_cos[LT ? q : 0] : tb_cos<R>(tab, q))));
       } else {
         y = add<R>(scl<R>(s, sn), d);
       }
-      a = mul<R>(y, tb_chirp<R>(tab, q));
+      a = mul<R>(y, chirp(q));
     }
     v[n2] = a;
   }
@@ -187,13 +210,13 @@ __global__ __launch_bounds__(KL * 16) void bluestein_kernel(const Tin* __restric
       c1sum.y += __shfl_xor(c1sum.y, o, 16);
     }
   }
-  __syncthreads();
+  wave_sync();
 
   // ---- forward FFT_P ----
   fftq<R, Q, false>(v);                                     // over n2 -> k2
 #pragma unroll
-  for (int k2 = 0; k2 < Q; ++k2) buf[g][kRow * t + k2] = mul<R>(v[k2], tb_tw<R>(tab, t * k2));
-  __syncthreads();
+  for (int k2 = 0; k2 < Q; ++k2) buf[g][kRow * t + k2] = mul<R>(v[k2], twiddle(t, k2));
+  wave_sync();
   constexpr int C = Q / 16;                                 // columns k2 = t + 16 c of this thread
   T2 u[C][16];
 #pragma unroll
@@ -203,29 +226,29 @@ __global__ __launch_bounds__(KL * 16) void bluestein_kernel(const Tin* __restric
     fft16<R, false>(u[c]);                                  // X[k2 + Q k1] in u[c][k1]
     // product with the kernel spectrum (1/P folded in), inverse FFT_16 over k1
 #pragma unroll
-    for (int k1 = 0; k1 < 16; ++k1) u[c][k1] = mul<R>(u[c][k1], tb_bhat<R>(tab, t + 16 * c + Q * k1));
+    for (int k1 = 0; k1 < 16; ++k1) u[c][k1] = mul<R>(u[c][k1], bhat(t + 16 * c + Q * k1));
     fft16<R, true>(u[c]);                                   // Z[n1] for column k2
   }
-  __syncthreads();
+  wave_sync();
 #pragma unroll
   for (int c = 0; c < C; ++c)
 #pragma unroll
     for (int n1 = 0; n1 < 16; ++n1) {
-      const T2 w = tb_tw<R>(tab, n1 * (t + 16 * c));
+      const T2 w = LT ? twiddle(t, n1) : tb_tw<R>(tab, n1 * (t + 16 * c));
       buf[g][kRow * n1 + t + 16 * c] = mul<R>(u[c][n1], mk2<R>(w.x, -w.y));
     }
-  __syncthreads();
+  wave_sync();
 #pragma unroll
   for (int k2 = 0; k2 < Q; ++k2) v[k2] = buf[g][kRow * t + k2];
   fftq<R, Q, true>(v);                                      // conv[t + 16 n2] in v[n2]
-  __syncthreads();
+  wave_sync();
   // Y_k = c_k conv_k, natural order
 #pragma unroll
   for (int n2 = 0; n2 < Q; ++n2) {
     const int k = t + 16 * n2;
-    if (k < M) buf[g][k] = mul<R>(v[n2], tb_chirp<R>(tab, k));
+    if (k < M) buf[g][k] = mul<R>(v[n2], chirp(k));
   }
-  __syncthreads();
+  wave_sync();
 
   // ---- post-processing: thread t takes j = J t .. J t + J - 1 (j <= (M - 1) / 2 <= 16 J - 1) ----
   constexpr int J = S::kOut;
@@ -269,7 +292,7 @@ __global__ __launch_bounds__(KL * 16) void bluestein_kernel(const Tin* __restric
     else
       od[uu] = add<R>(scl<R>(Y0, R(0.5)), run);                                // S_{2j+1}
   }
-  __syncthreads();
+  wave_sync();
   const R fs = INV ? R(1) : R(2) / R(M);
 #pragma unroll
   for (int uu = 0; uu < J; ++uu) {
@@ -287,42 +310,43 @@ __global__ __launch_bounds__(KL * 16) void bluestein_kernel(const Tin* __restric
       if (2 * j + 1 <= M - 2) buf[g][2 * j] = scl<R>(od[uu], fs);   // m = 2j + 1
     }
   }
-  __syncthreads();
+  if (AXIS == 1) __syncthreads();
+  else wave_sync();
   // ---- store (coalesced); with acc, out += result (all reads issued first) ----
   if (AXIS == 0) {
     if (acc) {
-      Tout o[KL][kPx];
+      Tout o[WL][kPx];
 #pragma unroll
-      for (int b = 0; b < KL; ++b)
+      for (int b = 0; b < WL; ++b)
 #pragma unroll
         for (int k = 0; k < kPx; ++k) {
-          const int p = tid + k * KL * 16;
-          if (b < nl && p < L) o[b][k] = out[gbase + size_t(b) * L + p];
+          const int p = wt + 64 * k, bl = w0 + b;
+          if (bl < nl && p < L) o[b][k] = out[gbase + size_t(bl) * L + p];
         }
 #pragma unroll
-      for (int b = 0; b < KL; ++b)
+      for (int b = 0; b < WL; ++b)
 #pragma unroll
         for (int k = 0; k < kPx; ++k) {
-          const int p = tid + k * KL * 16;
-          if (b < nl && p < L) {
-            const Tout w = cv<Tout>(buf[b][p]);
+          const int p = wt + 64 * k, bl = w0 + b;
+          if (bl < nl && p < L) {
+            const Tout w = cv<Tout>(buf[bl][p]);
             Tout r2;
             r2.x = o[b][k].x + w.x;
             r2.y = o[b][k].y + w.y;
-            out[gbase + size_t(b) * L + p] = r2;
+            out[gbase + size_t(bl) * L + p] = r2;
           }
         }
     } else {
 #pragma unroll
-      for (int b = 0; b < KL; ++b)
+      for (int b = 0; b < WL; ++b)
 #pragma unroll
         for (int k = 0; k < kPx; ++k) {
-          const int p = tid + k * KL * 16;
-          if (b < nl && p < L) out[gbase + size_t(b) * L + p] = cv<Tout>(buf[b][p]);
+          const int p = wt + 64 * k, bl = w0 + b;
+          if (bl < nl && p < L) out[gbase + size_t(bl) * L + p] = cv<Tout>(buf[bl][p]);
         }
     }
   } else {
-    constexpr int kPer = (KL * 256 + KL * 16 - 1) / (KL * 16);
+    constexpr int kPer = LT ? (P / 2 + 2 + 15) / 16 : 16;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
       const int e = tid + k * KL * 16;
@@ -350,14 +374,14 @@ void launch_b(bool neumann, bool inv, const Tin* in, Tout* out, int nlines, int 
 
 }  // namespace
 
-// lines per workgroup: 4 along x; along y 16 (complex64, P = 256), 8 (complex64 with P = 512 or
+// lines per workgroup: 4 along x (16 in complex64 with P = 256); along y 16 (complex64, P = 256), 8 (complex64 with P = 512 or
 // complex128 with P = 256), 4 (complex128, P = 512): LDS per workgroup 17-35 KB
 template <typename R, typename Tin, typename Tout>
 hipError_t launch_bluestein_x(bool neumann, bool inverse, const Tin* in, Tout* out, int nlines, int L,
                               const BluesteinTables& tab, hipStream_t s, int accumulate, const int* skip) {
   if (!bluestein_ok(tab.M) || L > 256 || tab.P != bluestein_length(tab.M)) return hipErrorInvalidValue;
   if (tab.P == 256)
-    launch_b<R, 0, 256, 4>(neumann, inverse, in, out, nlines, 0, L, 0, tab, s, accumulate, skip);
+    launch_b<R, 0, 256, sizeof(R) == 4 ? 16 : 4>(neumann, inverse, in, out, nlines, 0, L, 0, tab, s, accumulate, skip);
   else
     launch_b<R, 0, 512, 4>(neumann, inverse, in, out, nlines, 0, L, 0, tab, s, accumulate, skip);
   return hipGetLastError();

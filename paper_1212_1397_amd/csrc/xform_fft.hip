@@ -62,13 +62,6 @@ template <typename R> __device__ __forceinline__ void fft8(T2 (&v)[8]) {
   v[7] = sub<R>(a3, b3);
 }
 
-// LDS ordering between the lanes of one wave (its LDS accesses are executed in
-// order; the compiler must keep them in order too)
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 __device__ __forceinline__ constexpr int padi(int i) { return i + (i >> 3); }
 
 template <typename R, int M, int RAD, int NS>
