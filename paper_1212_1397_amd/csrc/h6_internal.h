@@ -174,11 +174,14 @@ constexpr int kScal = 4096;        // device scalar slots (double2)
 constexpr int kGramMax = 16;       // Gram row entries formed by launch_update_gram
 constexpr int kZSegs = 32;         // most segments per z line in the partitioned z solver
 constexpr int kMaxZ = kZSegs * 17; // largest n'z of the partitioned z solver
-// segments per z line: complex64 solves use 16 (32 modes per workgroup, 256-byte
-// row segments) up to n'z = 272; complex128 solves and longer lines use 32 (16
+// segments per z line: 8 up to n'z = 72, where the chain over the segments is the
+// longer part (apply_Pinv with 32 or 16 against 8, complex128 32^3 20.8 -> 18.1 us,
+// 128 x 128 x 24 65 -> 55, 70^3 44.8 -> 42.1; complex64 32^3 16.8 -> 15.7, 128 x 128 x
+// 64 60.7 -> 59.6); else complex64 solves use 16 (32 modes per workgroup, 256-byte
+// row segments) up to n'z = 272, complex128 solves and longer lines 32 (16
 // modes per workgroup, fewer registers per thread).  The segment-start table
 // is built for this count.
-inline int z_segments(int nz, bool f32) { return (f32 && nz <= 16 * 17) ? 16 : 32; }
+inline int z_segments(int nz, bool f32) { return nz <= 8 * 9 ? 8 : f32 && nz <= 16 * 17 ? 16 : 32; }
 
 // Workgroup id remap for the 8 XCDs of the chip: the hardware hands out
 // consecutive workgroup ids round-robin over the XCDs (each with its own L2);

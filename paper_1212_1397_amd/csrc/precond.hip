@@ -119,8 +119,9 @@ __device__ __forceinline__ typename C2<R>::T crecip(typename C2<R>::T b) {
 // entering from above (it is zero) and row n'z - 1 never sees the one from
 // below, so their missing off-diagonal needs no special case.
 // HBM traffic: one read and one write of the vector plus the small cstart table.
-// launch shapes: kLanes modes x kSegs segments = 512 threads; 32 x 16 up to
-// n'z = 272 (256-byte row segments), 16 x 32 above (n'z <= 544)
+// launch shapes: kLanes modes x kSegs segments; x 8 up to n'z = 72 (256-byte row
+// segments), 512 threads above: 32 x 16 in complex64 up to n'z = 272 (256-byte row
+// segments), 16 x 32 else (n'z <= 544)
 
 template <typename R, int kLanes, int kSegs, int kSmax>
 __global__ __launch_bounds__(kLanes * kSegs) void tridiag_z_kernel(
@@ -291,11 +292,16 @@ hipError_t pinv_impl(h6_plan P, const Tin* r, Tout* z, hipStream_t s, int part, 
     // 70 in complex64; 511 x 511 x 512 1420 -> 1042; 256 x 258 x 258 complex64 68 ->
     // 65).  Cache-resident ones do not (127 x 127 x 128 complex64 14 -> 16 us).
     const int remap = P->N * sizeof(T2) > (size_t(48) << 20);
-    auto go = [&](auto kern, int lanes) {
-      hipLaunchKernelGGL(kern, dim3((nx * ny + lanes - 1) / lanes), dim3(512), 0, s, w1, w0, cst,
+    auto go = [&](auto kern, int lanes, int threads = 512) {
+      hipLaunchKernelGGL(kern, dim3((nx * ny + lanes - 1) / lanes), dim3(threads), 0, s, w1, w0, cst,
                          P->d_lambda_x, P->d_lambda_y, P->d_zparams, nx, ny, nz, remap, P->skip);
     };
-    if (z_segments(nz, sizeof(R) == 4) == 16) {
+    const int segs = z_segments(nz, sizeof(R) == 4);
+    if (segs == 8) {
+      constexpr int kL = sizeof(R) == 4 ? 32 : 16;
+      if (nz <= 8 * 5) go(tridiag_z_kernel<R, kL, 8, 5>, kL, 8 * kL);
+      else go(tridiag_z_kernel<R, kL, 8, 9>, kL, 8 * kL);
+    } else if (segs == 16) {
       if (nz <= 16 * 5) go(tridiag_z_kernel<R, 32, 16, 5>, 32);
       else if (nz <= 16 * 9) go(tridiag_z_kernel<R, 32, 16, 9>, 32);
       else go(tridiag_z_kernel<R, 32, 16, 17>, 32);
