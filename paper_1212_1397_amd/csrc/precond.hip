@@ -302,9 +302,10 @@ hipError_t pinv_impl(h6_plan P, const Tin* r, Tout* z, hipStream_t s, int part, 
       if (nz <= 8 * 5) go(tridiag_z_kernel<R, kL, 8, 5>, kL, 8 * kL);
       else go(tridiag_z_kernel<R, kL, 8, 9>, kL, 8 * kL);
     } else if (segs == 16) {
-      if (nz <= 16 * 5) go(tridiag_z_kernel<R, 32, 16, 5>, 32);
-      else if (nz <= 16 * 9) go(tridiag_z_kernel<R, 32, 16, 9>, 32);
-      else go(tridiag_z_kernel<R, 32, 16, 17>, 32);
+      if constexpr (sizeof(R) == 4) {      // (complex64 only, see z_segments)
+        if (nz <= 16 * 9) go(tridiag_z_kernel<R, 32, 16, 9>, 32);
+        else go(tridiag_z_kernel<R, 32, 16, 17>, 32);
+      }
     } else {
       if (nz <= 32 * 9) go(tridiag_z_kernel<R, 16, 32, 9>, 16);
       else go(tridiag_z_kernel<R, 16, 32, 17>, 16);
