@@ -285,27 +285,22 @@ hipError_t build_bluestein(AxisXform& ax, hipStream_t s) {
   return e;
 }
 
-// Tables of the power-of-two FFT path (xform_fft.hip): twiddles exp(-2 pi i t / M)
-// and sin / cos(pi q / M), in double and in single precision, in one device
-// allocation.
+// Tables of the power-of-two FFT path (xform_fft.hip): exp(-2 pi i t / M) and
+// exp(-pi i q / M), in double and in single precision, in one device allocation.
 hipError_t build_fft(AxisXform& ax, hipStream_t s) {
   const int M = ax.M;
-  const size_t D = size_t(M) * sizeof(double2), bytes = 2 * D + D / 2 + D / 2;   // tw, sin + cos, tw_f, sin_f + cos_f
+  const size_t D = size_t(M) * sizeof(double2), bytes = 2 * D + D;      // tw, hw, tw_f, hw_f
   std::vector<char> host(bytes);
   double2* tw = reinterpret_cast<double2*>(host.data());
-  double* sq = reinterpret_cast<double*>(host.data() + D);
-  double* cq = sq + M;
-  float2* twf = reinterpret_cast<float2*>(host.data() + 2 * D);
-  float* sf = reinterpret_cast<float*>(host.data() + 2 * D + D / 2);
-  float* cf = sf + M;
+  double2* hw = tw + M;
+  float2* twf = reinterpret_cast<float2*>(hw + M);
+  float2* hwf = twf + M;
   for (int t = 0; t < M; ++t) {
-    const long double ang = -2.0L * M_PIl * (long double)t / M, half = M_PIl * (long double)t / M;
-    tw[t] = make_double2(double(cosl(ang)), double(sinl(ang)));
-    sq[t] = double(sinl(half));
-    cq[t] = double(cosl(half));
+    const long double half = M_PIl * (long double)t / M, ang = 2.0L * half;
+    tw[t] = make_double2(double(cosl(ang)), double(-sinl(ang)));
+    hw[t] = make_double2(double(cosl(half)), double(-sinl(half)));
     twf[t] = make_float2(float(tw[t].x), float(tw[t].y));
-    sf[t] = float(sq[t]);
-    cf[t] = float(cq[t]);
+    hwf[t] = make_float2(float(hw[t].x), float(hw[t].y));
   }
   char* mem = nullptr;
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&mem), bytes);
@@ -314,11 +309,9 @@ hipError_t build_fft(AxisXform& ax, hipStream_t s) {
   FftTables& t = ax.fft;
   t.M = M;
   t.tw = reinterpret_cast<const double2*>(mem);
-  t.sin_q = reinterpret_cast<const double*>(mem + D);
-  t.cos_q = t.sin_q + M;
+  t.hw = t.tw + M;
   t.tw_f = reinterpret_cast<const float2*>(mem + 2 * D);
-  t.sin_f = reinterpret_cast<const float*>(mem + 2 * D + D / 2);
-  t.cos_f = t.sin_f + M;
+  t.hw_f = t.tw_f + M;
   e = hipMemcpyAsync(mem, host.data(), bytes, hipMemcpyHostToDevice, s);
   return e == hipSuccess ? hipStreamSynchronize(s) : e;
 }

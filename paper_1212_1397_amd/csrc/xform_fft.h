@@ -9,11 +9,9 @@ namespace h6 {
 struct FftTables {
   int M = 0;                       // period parameter (a power of two)
   const double2* tw = nullptr;     // exp(-2 pi i t / M), t = 0..M-1
-  const double* sin_q = nullptr;   // sin(pi q / M), q = 0..M-1
-  const double* cos_q = nullptr;   // cos(pi q / M), q = 0..M-1
+  const double2* hw = nullptr;     // exp(-pi i q / M), q = 0..M-1
   const float2* tw_f = nullptr;    // the same tables rounded to single precision (complex64 path)
-  const float* sin_f = nullptr;
-  const float* cos_f = nullptr;
+  const float2* hw_f = nullptr;
 };
 
 inline bool fft_ok(int M) { return M == 64 || M == 128 || M == 256 || M == 512; }

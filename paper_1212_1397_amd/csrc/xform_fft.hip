@@ -1,27 +1,31 @@
 // Fast sine / cosine transforms of Section 3.3 for power-of-two period
 // parameters M = n + 1 (the grids h = 1/64 .. 1/512 of Section 4's tables).
 //
-// The reduction to one complex DFT of length M per line is the one of
-// xform_rader.hip (it holds for every M): with s_q = x_q + x_{M-q} and
-// d_q = x_q - x_{M-q}, y_q = s_q sin(pi q / M) + d_q (sine basis) or
-// y_q = s_q + d_q sin(pi q / M) (cosine basis), q = 1..M-1, y_0 = 0,
-// Y = DFT_M(y), the even outputs from Y_j +- Y_{M-j} and the odd ones from a
-// running sum of them.
+// A line's odd (sine) or even (cosine) extension to period 2 M has the transform as
+// its DFT of length 2 M.  The first step of that DFT, with s_q = x_q + x_{M-q} and
+// d_q = x_q - x_{M-q}, q = 1..M-1, leaves two DFTs of length M:
+//   even outputs: of d (sine; S_2j = i/2 D_j), of s (cosine; C_2j = S_j / 2);
+//   odd outputs: of s_q exp(-i pi q / M) and of d_q exp(-i pi q / M), the same way,
+// with zeros at q = 0 in the sine basis and 2 (x_0 +- x_M) in the cosine basis.  Only
+// j <= M / 2 of each is formed in the last stage.  One DFT of s_q sin(pi q / M) + d_q
+// would do instead of two, but leaves the odd outputs as running sums over j, which
+// gather the rounding errors of all values before: complex128, sine, M = 64 .. 512,
+// white noise: 7.0e-16 .. 2.4e-15 relative that way, 1.7e-16 .. 2.1e-16 this way,
+// 2.0e-16 .. 5.3e-16 the dense product (on a CPU; complex64 in proportion).
 //
 // DFT_M by Stockham's autosort algorithm in radix 8 (last stages radix 4 where
-// 8 does not divide): M / 8 lanes per line, eight values each, natural order in
-// and out; a stage with Ns values already combined takes butterfly b's inputs
-// from b + r M / R, times exp(-2 pi i (b mod Ns) r / (Ns R)), and puts its
+// 8 does not divide): M / 8 lanes per line, eight values of each sequence per lane,
+// natural order in and out; a stage with Ns values already combined takes butterfly b's
+// inputs from b + r M / R, times exp(-2 pi i (b mod Ns) r / (Ns R)), and puts its
 // outputs at (b div Ns) Ns R + (b mod Ns) + r Ns.  A line's lanes sit in one
-// wave, so the exchanges between stages (LDS, one pad value per eight) need no
-// workgroup barrier; only the loads and stores of y columns, which the whole
-// workgroup shares, do.  Eight values per lane keep the registers low enough
-// for the loads of other waves to hide behind these: the passes are bound by
-// memory.  Against the dense product of the slab kernels (averages of forward
-// and inverse): 511 x 511 x 512 complex128 x 2785 -> 843 us (5.1 TB/s), y 2805 ->
-// 1025; 255 x 255 x 256 complex128 x 199 -> 112, y 230 -> 129, complex64 131 -> 84,
-// 132 -> 72; 127^3 complex64 17.8 -> 14.6, 18.8 -> 14.6; 63^3 9.6 -> 6.9, 9.7 -> 7.7.
-// Errors against 64 bits are the dense product's within 2 %.
+// wave, so the exchanges between stages (LDS, one pad value per eight, both sequences
+// through the same buffer) need no workgroup barrier; only the loads and stores of y
+// columns, which the whole workgroup shares, do.  Bound by memory, but for the y
+// columns of M = 256 and 512, where the registers of two sequences leave four waves per
+// SIMD.  Sine, averages of forward and inverse, dense product (slab kernels) -> this:
+// 511 x 511 x 512 complex128 x 2773 -> 915 us (4.7 TB/s), y 2782 -> 1074, complex64 1428
+// -> 653, 1488 -> 660; 255 x 255 x 256 204 -> 114, 229 -> 131, 135 -> 89, 132 -> 79;
+// 127 x 127 x 128 22.7 -> 20.1, 24.1 -> 19.7, 17.5 -> 14.5, 18.5 -> 15.1.
 #include "fft16.h"
 #include "h6_internal.h"
 #include "xform_fft.h"
@@ -36,11 +40,8 @@ using namespace fftdev;
 template <typename R> __device__ __forceinline__ T2 tf_tw(const FftTables& t, int i) {
   if constexpr (sizeof(R) == 4) return t.tw_f[i]; else return t.tw[i];
 }
-template <typename R> __device__ __forceinline__ R tf_sin(const FftTables& t, int i) {
-  if constexpr (sizeof(R) == 4) return t.sin_f[i]; else return t.sin_q[i];
-}
-template <typename R> __device__ __forceinline__ R tf_cos(const FftTables& t, int i) {
-  if constexpr (sizeof(R) == 4) return t.cos_f[i]; else return t.cos_q[i];
+template <typename R> __device__ __forceinline__ T2 tf_hw(const FftTables& t, int i) {
+  if constexpr (sizeof(R) == 4) return t.hw_f[i]; else return t.hw[i];
 }
 
 // forward FFT of length 8 in registers (natural order in and out)
@@ -65,22 +66,8 @@ template <typename R> __device__ __forceinline__ void fft8(T2 (&v)[8]) {
 __device__ __forceinline__ constexpr int padi(int i) { return i + (i >> 3); }
 
 template <typename R, int M, int RAD, int NS>
-__device__ __forceinline__ void stage_in(T2 (&v)[8], const T2* buf, int t, const FftTables& tab) {
-  constexpr int T = M / 8, NB = 8 / RAD;      // lanes per line, butterflies per lane
-#pragma unroll
-  for (int u = 0; u < NB; ++u) {
-    const int b = t + T * u, k = b & (NS - 1);
-#pragma unroll
-    for (int r = 0; r < RAD; ++r) {
-      T2 x = buf[padi(b + r * (M / RAD))];
-      if (r > 0) x = mul<R>(x, tf_tw<R>(tab, k * r * (M / (NS * RAD))));
-      v[u * RAD + r] = x;
-    }
-  }
-}
-template <typename R, int M, int RAD, int NS>
 __device__ __forceinline__ void stage_out(const T2 (&v)[8], T2* buf, int t) {
-  constexpr int T = M / 8, NB = 8 / RAD;
+  constexpr int T = M / 8, NB = 8 / RAD;      // lanes per line, butterflies per lane
 #pragma unroll
   for (int u = 0; u < NB; ++u) {
     const int b = t + T * u;
@@ -89,27 +76,72 @@ __device__ __forceinline__ void stage_out(const T2 (&v)[8], T2* buf, int t) {
     for (int r = 0; r < RAD; ++r) buf[padi(o + r * NS)] = v[u * RAD + r];
   }
 }
-template <typename R, int M, int RAD, int NS>
-__device__ __forceinline__ void stage(T2 (&v)[8], T2* buf, int t, const FftTables& tab) {
-  stage_in<R, M, RAD, NS>(v, buf, t, tab);
-  if constexpr (RAD == 8) {
-    fft8<R>(v);
-  } else {
-    fft4<R, false>(v[0], v[1], v[2], v[3]);
-    fft4<R, false>(v[4], v[5], v[6], v[7]);
-  }
-  wave_sync();
-  stage_out<R, M, RAD, NS>(v, buf, t);
-  wave_sync();
+
+template <typename R, int M, int RAD>
+__device__ __forceinline__ void stage_in(T2 (&v)[8], const T2* buf, int t) {
+  constexpr int T = M / 8, NB = 8 / RAD;
+#pragma unroll
+  for (int u = 0; u < NB; ++u)
+#pragma unroll
+    for (int r = 0; r < RAD; ++r) v[u * RAD + r] = buf[padi(t + T * u + r * (M / RAD))];
+}
+
+// Keeps the compiler from spreading loads ahead over steps that hold both sequences, so
+// that the kernels fit the registers of four waves per SIMD (complex128 sine: 511 x 511 x
+// 128 y 324 -> 272 us, 255 x 255 x 256 y 153 -> 130, x 122 -> 111).  Not for complex64
+// x lines (255 x 255 x 256 87 against 91).
+template <bool TIGHT> __device__ __forceinline__ void in_order() {
+  if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
+}
+
+// The two sequences from the outputs of a stage of radix RAD0, NS0 values combined before
+// it, through the line's buffer (one after the other) to the outputs of the next, of radix
+// RAD; they share its factors.
+template <typename R, int M, int RAD0, int NS0, int RAD, bool TIGHT>
+__device__ __forceinline__ void stage(T2 (&e)[8], T2 (&o)[8], T2* buf, int t, const FftTables& tab) {
+  constexpr int T = M / 8, NB = 8 / RAD, NS = NS0 * RAD0;
+  T2 w[8];
+  auto factors = [&]() {
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+#pragma unroll
+      for (int r = 1; r < RAD; ++r) w[u * RAD + r] = tf_tw<R>(tab, ((t + T * u) & (NS - 1)) * r * (M / (NS * RAD)));
+  };
+  auto pass = [&](T2 (&v)[8]) {
+    wave_sync();
+    stage_out<R, M, RAD0, NS0>(v, buf, t);
+    wave_sync();
+    stage_in<R, M, RAD>(v, buf, t);
+  };
+  auto combine = [&](T2 (&v)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (i % RAD > 0) v[i] = mul<R>(v[i], w[i]);
+    if constexpr (RAD == 8) {
+      fft8<R>(v);
+    } else {
+      fft4<R, false>(v[0], v[1], v[2], v[3]);
+      fft4<R, false>(v[4], v[5], v[6], v[7]);
+    }
+  };
+  if (!TIGHT) factors();
+  pass(e);
+  pass(o);
+  in_order<TIGHT>();
+  if (TIGHT) factors();
+  combine(e);
+  in_order<TIGHT>();
+  combine(o);
 }
 
 template <typename R, int AXIS, bool NEU, bool INV, int M, int KL, typename Tin, typename Tout>
-__global__ __launch_bounds__(KL * M / 8) void fft_kernel(const Tin* __restrict__ in, Tout* __restrict__ out,
-                                                         int nlines, int nx, FftTables tab, int acc,
-                                                         const int* __restrict__ skip) {
+__global__ __launch_bounds__(KL * M / 8, sizeof(R) == 8 && AXIS == 1 ? 4 : 1) void fft_kernel(
+    const Tin* __restrict__ in, Tout* __restrict__ out, int nlines, int nx, FftTables tab, int acc,
+    const int* __restrict__ skip) {
   if (skip && *skip) return;
   constexpr int T = M / 8, L = NEU ? M + 1 : M - 1, OFF = NEU ? 0 : -1;   // array index of node q: q + OFF
   constexpr int NTH = KL * T;
+  constexpr bool TIGHT = AXIS == 1 || sizeof(R) == 8;
   constexpr int STR = M + M / 8 + (AXIS == 1 ? 1 : 2);                    // LDS values per line (>= padi(M) + 1)
   __shared__ T2 buf[KL][STR];
   const int tid = threadIdx.x, g = tid / T, t = tid % T;
@@ -128,7 +160,9 @@ __global__ __launch_bounds__(KL * M / 8) void fft_kernel(const Tin* __restrict__
     nl = min(KL, nx - bx * KL);
     gbase = size_t(by) * nx * L + bx * KL;
   }
-  // ---- load: x lines by their own lanes, y columns by the whole workgroup ----
+  // ---- load: x lines by their own lanes, y columns by the whole workgroup; the sine
+  // basis has zeros at the end nodes ----
+  if (!NEU && t == 0) line[padi(0)] = line[padi(M)] = mk2<R>(0, 0);
   if (AXIS == 0) {
     constexpr int NP = (L + T - 1) / T;
     if (g < nl) {
@@ -156,107 +190,58 @@ __global__ __launch_bounds__(KL * M / 8) void fft_kernel(const Tin* __restrict__
     }
     __syncthreads();
   }
-  // ---- y_q for q = t + T r, first stage in registers ----
-  T2 v[8];
-  T2 c1sum = mk2<R>(0, 0), xa = mk2<R>(0, 0), xb = mk2<R>(0, 0);
-  if (NEU) {
-    xa = line[padi(0)];
-    xb = line[padi(M)];
-    if (!INV) {
-      xa = scl<R>(xa, R(0.5));
-      xb = scl<R>(xb, R(0.5));
-    }
-  }
+  // ---- the two sequences at q = t + T r ----
+  T2 ev[8], od[8];
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     const int q = t + T * r;
-    const bool ok = r > 0 || t > 0;
-    const T2 xq = line[padi(ok ? q : 1)], xr = line[padi(ok ? M - q : 1)];
-    const T2 s = add<R>(xq, xr), d = sub<R>(xq, xr);
-    const R sn = tf_sin<R>(tab, q);
-    T2 y;
-    if (NEU) {
-      y = add<R>(s, scl<R>(d, sn));
-      c1sum = add<R>(c1sum, scl<R>(d, R(0.5) * tf_cos<R>(tab, q)));      // q = 0: d = 0
-    } else {
-      y = add<R>(scl<R>(s, sn), d);
-    }
-    v[r] = ok ? y : mk2<R>(0, 0);
+    const T2 xq = line[padi(q)], xr = line[padi(M - q)];
+    const T2 s = add<R>(xq, xr), d = sub<R>(xq, xr), w = tf_hw<R>(tab, q);
+    ev[r] = NEU ? s : d;
+    od[r] = mul<R>(NEU ? d : s, w);
+    if (r == 3) in_order<TIGHT>();
   }
-  if (NEU) {
-#pragma unroll
-    for (int o = T / 2; o > 0; o >>= 1) {
-      c1sum.x += __shfl_xor(c1sum.x, o, T);
-      c1sum.y += __shfl_xor(c1sum.y, o, T);
-    }
+  if (NEU && INV && t == 0) {      // the end nodes enter twice (forward: with half their value)
+    ev[0] = scl<R>(ev[0], R(2));
+    od[0] = scl<R>(od[0], R(2));
   }
-  fft8<R>(v);
-  wave_sync();
-  stage_out<R, M, 8, 1>(v, line, t);
-  wave_sync();
+  in_order<TIGHT>();
+  fft8<R>(ev);
+  in_order<TIGHT>();
+  fft8<R>(od);
+  in_order<TIGHT>();
   if constexpr (M == 64) {
-    stage<R, M, 8, 8>(v, line, t, tab);
+    stage<R, M, 8, 1, 8, TIGHT>(ev, od, line, t, tab);
   } else if constexpr (M == 128) {
-    stage<R, M, 4, 8>(v, line, t, tab);
-    stage<R, M, 4, 32>(v, line, t, tab);
+    stage<R, M, 8, 1, 4, TIGHT>(ev, od, line, t, tab);
+    stage<R, M, 4, 8, 4, TIGHT>(ev, od, line, t, tab);
   } else if constexpr (M == 256) {
-    stage<R, M, 8, 8>(v, line, t, tab);
-    stage<R, M, 4, 64>(v, line, t, tab);
+    stage<R, M, 8, 1, 8, TIGHT>(ev, od, line, t, tab);
+    stage<R, M, 8, 8, 4, TIGHT>(ev, od, line, t, tab);
   } else {
-    stage<R, M, 8, 8>(v, line, t, tab);
-    stage<R, M, 8, 64>(v, line, t, tab);
+    stage<R, M, 8, 1, 8, TIGHT>(ev, od, line, t, tab);
+    stage<R, M, 8, 8, 8, TIGHT>(ev, od, line, t, tab);
   }
-  // ---- post-processing: lane t takes j = 4t .. 4t + 3 (and j = M / 2 for C_M);
-  // the odd outputs need running sums over j ----
-  T2 ev[4], od[4];
-  const T2 Y0 = line[padi(0)];
-  T2 loc = mk2<R>(0, 0);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int j = 4 * t + u;
-    const T2 Yj = line[padi(j)], Ym = line[padi(j == 0 ? 0 : M - j)];
-    T2 inc = NEU ? scl<R>(sub<R>(Yj, Ym), R(0.5)) : scl<R>(add<R>(Yj, Ym), R(0.5));
-    if (j == 0) inc = mk2<R>(0, 0);
-    loc = add<R>(loc, inc);
-    od[u] = loc;
-    if (NEU) {
-      const T2 A = scl<R>(add<R>(Yj, Ym), R(0.25));
-      ev[u] = add<R>(add<R>(xa, xb), A);                          // C_{2j}
-    } else {
-      const T2 D = sub<R>(Yj, Ym);
-      ev[u] = mk2<R>(-R(0.25) * D.y, R(0.25) * D.x);              // S_{2j}
-    }
-  }
-  T2 last = mk2<R>(0, 0);
-  if (NEU) last = add<R>(add<R>(xa, xb), scl<R>(line[padi(M / 2)], R(0.5)));   // C_M
-  T2 sc = loc;
-#pragma unroll
-  for (int o = 1; o < T; o <<= 1) {
-    const R px = __shfl_up(sc.x, o, T), py = __shfl_up(sc.y, o, T);
-    if (t >= o) {
-      sc.x += px;
-      sc.y += py;
-    }
-  }
-  const T2 before = sub<R>(sc, loc);                              // sum over the lanes before t
+  // ---- outputs m = 2j (ev) and 2j + 1 (od), j < M / 2, to the line in array order: value
+  // u RAD + r of the last stage is j = t + T u + r M / RAD ----
   wave_sync();
-  // scaled outputs in array order over the line
-  const R fs = INV ? R(1) : R(2) / R(M);
+  constexpr int RAD = M == 64 || M == 512 ? 8 : 4;
+  const R fs = INV ? R(0.5) : R(1) / R(M);
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int j = 4 * t + u;
-    const T2 run = add<R>(before, od[u]);
-    if (NEU) {
-      const T2 o = add<R>(sub<R>(xa, xb), add<R>(c1sum, mk2<R>(run.y, -run.x)));      // C_{2j+1}
-      line[padi(2 * j)] = scl<R>(ev[u], (!INV && j == 0) ? R(0.5) * fs : fs);
-      line[padi(2 * j + 1)] = scl<R>(o, fs);
-    } else {
-      const T2 o = add<R>(scl<R>(Y0, R(0.5)), run);                                    // S_{2j+1}
-      if (j > 0) line[padi(2 * j - 1)] = scl<R>(ev[u], fs);
-      line[padi(2 * j)] = scl<R>(o, fs);
+  for (int u = 0; u < 8 / RAD; ++u)
+#pragma unroll
+    for (int r = 0; r < RAD / 2; ++r) {
+      const int j = t + T * u + r * (M / RAD);
+      const T2 a = ev[u * RAD + r], b = od[u * RAD + r];
+      if (NEU) {
+        line[padi(2 * j)] = scl<R>(a, (!INV && j == 0) ? R(0.5) * fs : fs);
+        line[padi(2 * j + 1)] = scl<R>(b, fs);
+      } else {                                            // i / 2 times the DFT's
+        if (j > 0) line[padi(2 * j - 1)] = mk2<R>(-fs * a.y, fs * a.x);
+        line[padi(2 * j)] = mk2<R>(-fs * b.y, fs * b.x);
+      }
     }
-  }
-  if (NEU && t == 0) line[padi(M)] = scl<R>(last, INV ? fs : R(0.5) * fs);
+  if (NEU && t == 0) line[padi(M)] = scl<R>(ev[RAD / 2], INV ? fs : R(0.5) * fs);      // j = M / 2
   // ---- store (coalesced); with acc, out += result ----
   if (AXIS == 0) {
     wave_sync();
@@ -324,10 +309,9 @@ hipError_t launch_fft_x(bool neumann, bool inverse, const Tin* in, Tout* out, in
   return hipGetLastError();
 }
 
-// columns per workgroup along y: 16 (128- and 256-byte row segments), 32 for
-// M = 64; at M = 512 complex128 columns take 8 (36 KB of LDS per 4 lines: 16
-// would leave one workgroup per CU, 1230 against 1025 us at 511 x 511 x 512;
-// complex64 573 against 613 us the other way round)
+// columns per workgroup along y: 32 for M = 64, 16 for 128 and 256 (128- and 256-byte row
+// segments), 8 for 512, where 16 leave a CU one workgroup (complex64 511 x 511 x 128, sine
+// and cosine: 190 + 177 us with 16, 173 + 184 with 8)
 template <typename R, typename T>
 hipError_t launch_fft_y(bool neumann, bool inverse, const T* in, T* out, int nx, int L, int nz, const FftTables& tab,
                         hipStream_t s, const int* skip) {
@@ -336,7 +320,7 @@ hipError_t launch_fft_y(bool neumann, bool inverse, const T* in, T* out, int nx,
     case 64: launch_f<R, 1, 64, 32>(neumann, inverse, in, out, 0, nx, nz, tab, s, 0, skip); break;
     case 128: launch_f<R, 1, 128, 16>(neumann, inverse, in, out, 0, nx, nz, tab, s, 0, skip); break;
     case 256: launch_f<R, 1, 256, 16>(neumann, inverse, in, out, 0, nx, nz, tab, s, 0, skip); break;
-    case 512: launch_f<R, 1, 512, (sizeof(R) == 4 ? 16 : 8)>(neumann, inverse, in, out, 0, nx, nz, tab, s, 0, skip); break;
+    case 512: launch_f<R, 1, 512, 8>(neumann, inverse, in, out, 0, nx, nz, tab, s, 0, skip); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
