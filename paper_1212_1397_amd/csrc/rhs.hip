@@ -454,7 +454,9 @@ hipError_t launch_rhs(h6_plan P, int nsrc, const double* centres, const double* 
   RhsArgs a{};
   a.c = rhs_coef(P);
   a.nsrc = nsrc;
-  a.inv_sigma = 1.0 / sigma;
+  // no source: the row kernel still multiplies a factor by zero, so it has to be finite
+  // (1 / sigma and its fourth power overflow for the smallest sigma)
+  a.inv_sigma = nsrc > 0 ? 1.0 / sigma : 0.0;
   for (int i = 0; i < nsrc; ++i) {
     a.cx[i] = centres[3 * i];
     a.cy[i] = centres[3 * i + 1];
