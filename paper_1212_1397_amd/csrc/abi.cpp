@@ -167,16 +167,19 @@ void z_tridiagonal(h6_plan P, std::vector<cplx>& sub, std::vector<cplx>& diag,
 
 // Gaussian elimination of every z system T_z + (kappa + lx + ly) I: a pivot
 // below 1e-12 (4 + |shift|) or non-finite means A_p is singular.  Records
-// c'_{r0-1}, the value entering each of the kZSegs segments of rows
-// [r0, r0 + S), S = ceil(n'z / kZSegs), for the partitioned device solver.
+// c'_{r-1}, the value entering each start row r of z_start_rows, for the
+// partitioned device solver.
 bool factor_modes(h6_plan P, const std::vector<double>& lx, const std::vector<double>& ly,
                   const std::vector<cplx>& sub, const std::vector<cplx>& diag,
                   const std::vector<cplx>& sup, std::vector<cplx>& cstart, std::string& where) {
   const int L = P->dims[2];
   const size_t nmodes = lx.size() * ly.size();
-  const int segs = z_segments(L, P->p.precision == H6_MIXED);
-  const int S = (L + segs - 1) / segs;
-  cstart.assign(size_t(segs) * nmodes, cplx(0.0));
+  const bool f32 = P->p.precision == H6_MIXED;
+  const ZStarts st = z_start_rows(L, f32);
+  std::vector<int> start(L, -1);                     // row -> its entry of the table
+  for (int e = 0; e < z_starts(L, f32); ++e)
+    if (st.row(e) < L) start[st.row(e)] = e;
+  cstart.assign(size_t(z_starts(L, f32)) * nmodes, cplx(0.0));
   for (size_t j = 0; j < ly.size(); ++j)
     for (size_t i = 0; i < lx.size(); ++i) {
       const size_t mode = i + lx.size() * j;
@@ -184,7 +187,7 @@ bool factor_modes(h6_plan P, const std::vector<double>& lx, const std::vector<do
       const double tol = 1e-12 * (4.0 + std::abs(shift));
       cplx cprev = 0.0;
       for (int l = 0; l < L; ++l) {
-        if (l % S == 0) cstart[size_t(l / S) * nmodes + mode] = cprev;
+        if (start[l] >= 0) cstart[size_t(start[l]) * nmodes + mode] = cprev;
         const cplx piv = diag[l] + shift - (l > 0 ? sub[l] * cprev : cplx(0.0));
         if (!std::isfinite(piv.real()) || !std::isfinite(piv.imag()) || std::abs(piv) <= tol) {
           where = "zero pivot in z row " + std::to_string(l) + " of mode (" + std::to_string(i) +

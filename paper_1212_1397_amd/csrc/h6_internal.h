@@ -122,7 +122,7 @@ struct h6_plan_s {
   double* d_lambda_y = nullptr;
   h6::ZEnds zends{};                // end rows of the z tridiagonal (scaled form)
   double* d_zparams = nullptr;      // device copy for the z solver: kappa (re, im), then zends (kZParams doubles)
-  void* d_cstart = nullptr;         // Thomas c' entering each z segment: [z_segments(n'z)][n'x n'y], complex
+  void* d_cstart = nullptr;         // Thomas c' entering the start rows: [z_starts(n'z)][n'x n'y], complex
                                     // (double2, or float2 in mixed plans)
 
   // preconditioner workspace (complex128 vectors, or complex64 in mixed plans)
@@ -179,9 +179,22 @@ constexpr int kMaxZ = kZSegs * 17; // largest n'z of the partitioned z solver
 // 128 x 128 x 24 65 -> 55, 70^3 44.8 -> 42.1; complex64 32^3 16.8 -> 15.7, 128 x 128 x
 // 64 60.7 -> 59.6); else complex64 solves use 16 (32 modes per workgroup, 256-byte
 // row segments) up to n'z = 272, complex128 solves and longer lines 32 (16
-// modes per workgroup, fewer registers per thread).  The segment-start table
-// is built for this count.
+// modes per workgroup, fewer registers per thread).
 inline int z_segments(int nz, bool f32) { return nz <= 8 * 9 ? 8 : f32 && nz <= 16 * 17 ? 16 : 32; }
+// Rows whose entering c' the plan stores, from 64-bit elimination: 16 or 32 per line, so
+// that no thread replays c' over more than ceil(n'z / 16) or ceil(n'z / 32) rows.  Its
+// rounding errors grow along the rows of a mode near resonance: started once per segment
+// of eight, complex64 32^3 had 1.2 to 1.8 times the error (kh = 0.3, 0.6).
+inline int z_starts(int nz, bool f32) { return f32 && nz <= 16 * 17 ? 16 : 32; }
+// row of start e (n'z or more: none), and rows between the starts of one segment
+struct ZStarts {
+  int per, S, G;      // starts and rows per segment, rows per start
+  __host__ __device__ int row(int e) const { return e % per * G < S ? e / per * S + e % per * G : 1 << 30; }
+};
+inline ZStarts z_start_rows(int nz, bool f32) {
+  const int segs = z_segments(nz, f32), per = z_starts(nz, f32) / segs, S = (nz + segs - 1) / segs;
+  return ZStarts{per, S, (S + per - 1) / per};
+}
 
 // Workgroup id remap for the 8 XCDs of the chip: the hardware hands out
 // consecutive workgroup ids round-robin over the XCDs (each with its own L2);

@@ -107,9 +107,10 @@ __device__ __forceinline__ typename C2<R>::T crecip(typename C2<R>::T b) {
 //   x_i  = d'_i - p_i x_{i+1}                               (affine in x_{i+1}).
 // A workgroup owns kLanes consecutive modes (lanes) and splits every z line
 // into kSegs segments of S <= kSmax rows, one thread each, rows held in
-// registers.  The c' value entering each segment depends only on the matrix,
-// so the plan stores it (cstart[seg][mode], computed in FP64 at setup with the
-// pivot check).  Each thread replays c' over its rows and composes both affine
+// registers.  The c' value entering a row depends only on the matrix,
+// so the plan stores it for each segment's first row and, of long ones, for up to
+// three rows more (cstart[start][mode], z_start_rows, computed in FP64 at setup with
+// the pivot check).  Each thread replays c' from there over its rows and composes both affine
 // maps over its segment: their linear parts are the same product of -p_i, so
 // one product serves the forward and the backward chain.  The segment maps are
 // chained in order by the first segment's threads, which leave every segment its
@@ -123,12 +124,12 @@ __device__ __forceinline__ typename C2<R>::T crecip(typename C2<R>::T b) {
 // segments), 512 threads above: 32 x 16 in complex64 up to n'z = 272 (256-byte row
 // segments), 16 x 32 else (n'z <= 544)
 
-template <typename R, int kLanes, int kSegs, int kSmax>
+template <typename R, int kLanes, int kSegs, int kSmax, int kPer>
 __global__ __launch_bounds__(kLanes * kSegs) void tridiag_z_kernel(
     const typename C2<R>::T* __restrict__ in, typename C2<R>::T* __restrict__ out,
     const typename C2<R>::T* __restrict__ cstart, const double* __restrict__ lx,
     const double* __restrict__ ly, const double* __restrict__ zp, int nx, int ny, int nz, int remap,
-    const int* __restrict__ skip) {
+    int G, const int* __restrict__ skip) {
   if (skip && *skip) return;
   // kappa and the scaled end rows (ZEnds), from device memory (kZParams doubles)
   const double kap_re = zp[0], kap_im = zp[1];
@@ -154,7 +155,9 @@ __global__ __launch_bounds__(kLanes * kSegs) void tridiag_z_kernel(
   const T2 one = mk<R>(1, 0), zero = mk<R>(0, 0);
 
   // global reads up front, with clamped indices
-  const T2 cst = cstart[size_t(seg) * nmodes + mc];
+  T2 cst[kPer];                // entering c' of rows r0, r0 + G, ..
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) cst[k] = cstart[size_t(seg * kPer + k) * nmodes + mc];
   const double lxi = lx[i], lyj = ly[j];
   T2 d[kSmax], p[kSmax];     // right-hand side, then d'; inverse pivots p_i
 #pragma unroll
@@ -172,13 +175,16 @@ __global__ __launch_bounds__(kLanes * kSegs) void tridiag_z_kernel(
 
   // local pass: inverse pivots from the stored c', and the affine map
   // d'_{last} = Q d'_{r0-1} + B
-  T2 cprev = cst, Q = one, B = zero;
+  T2 cprev = cst[0], Q = one, B = zero;
 #pragma unroll
   for (int u = 0; u < kSmax; ++u) {
     if (u < cnt) {
       T2 b = bM;
       if (u == 0 && first) b = bF;
       if (u == uL && last) b = bL;
+#pragma unroll
+      for (int k = 1; k < kPer; ++k)
+        if (u == k * G) cprev = cst[k];
       p[u] = crecip<R>(csub<R>(b, cprev));
       Q = cmulr<R>(mk<R>(-p[u].x, -p[u].y), Q);
       B = cmulr<R>(p[u], csub<R>(d[u], B));
@@ -294,21 +300,23 @@ hipError_t pinv_impl(h6_plan P, const Tin* r, Tout* z, hipStream_t s, int part, 
     const int remap = P->N * sizeof(T2) > (size_t(48) << 20);
     auto go = [&](auto kern, int lanes, int threads = 512) {
       hipLaunchKernelGGL(kern, dim3((nx * ny + lanes - 1) / lanes), dim3(threads), 0, s, w1, w0, cst,
-                         P->d_lambda_x, P->d_lambda_y, P->d_zparams, nx, ny, nz, remap, P->skip);
+                         P->d_lambda_x, P->d_lambda_y, P->d_zparams, nx, ny, nz, remap,
+                         z_start_rows(nz, sizeof(R) == 4).G, P->skip);
     };
     const int segs = z_segments(nz, sizeof(R) == 4);
     if (segs == 8) {
       constexpr int kL = sizeof(R) == 4 ? 32 : 16;
-      if (nz <= 8 * 5) go(tridiag_z_kernel<R, kL, 8, 5>, kL, 8 * kL);
-      else go(tridiag_z_kernel<R, kL, 8, 9>, kL, 8 * kL);
+      constexpr int kPer = sizeof(R) == 4 ? 2 : 4;
+      if (nz <= 8 * 5) go(tridiag_z_kernel<R, kL, 8, 5, kPer>, kL, 8 * kL);
+      else go(tridiag_z_kernel<R, kL, 8, 9, kPer>, kL, 8 * kL);
     } else if (segs == 16) {
       if constexpr (sizeof(R) == 4) {      // (complex64 only, see z_segments)
-        if (nz <= 16 * 9) go(tridiag_z_kernel<R, 32, 16, 9>, 32);
-        else go(tridiag_z_kernel<R, 32, 16, 17>, 32);
+        if (nz <= 16 * 9) go(tridiag_z_kernel<R, 32, 16, 9, 1>, 32);
+        else go(tridiag_z_kernel<R, 32, 16, 17, 1>, 32);
       }
     } else {
-      if (nz <= 32 * 9) go(tridiag_z_kernel<R, 16, 32, 9>, 16);
-      else go(tridiag_z_kernel<R, 16, 32, 17>, 16);
+      if (nz <= 32 * 9) go(tridiag_z_kernel<R, 16, 32, 9, 1>, 16);
+      else go(tridiag_z_kernel<R, 16, 32, 17, 1>, 16);
     }
   }
   timing_end(P, KC_TRIDIAG, s, ev, Nd * 2 * sizeof(T2));

@@ -829,7 +829,7 @@ h6_status queue_create(h6_plan* plans, int count, int m, int lanes, h6_queue* ou
     if (e == hipSuccess) e = launch_reduce_sum_skip(P->partials, nparts, c.dev + kNorm, &lane->idle, ln.s);
     if (e == hipSuccess) e = launch_lane_check(lane, q, Q->d_head + ln.group, qn, c.dev + kNorm, Q->d_res, ln.s);
     if (e == hipSuccess) {
-      const size_t cst_bytes = size_t(z_segments(P->dims[2], mixed)) * P->dims[0] * P->dims[1] *
+      const size_t cst_bytes = size_t(z_starts(P->dims[2], mixed)) * P->dims[0] * P->dims[1] *
                                (mixed ? sizeof(float2) : sizeof(double2));
       const LaneRefill a{lane, q, ln.F, ln.U, P->V, P->d_stencil, P->d_cstart, P->d_zparams, P->N,
                          cst_bytes / 8, P->partials};
