@@ -28,6 +28,8 @@
 //
 // Gaussian derivatives: d^n/dx^n exp(-t^2/2), t = (x - c)/sigma, equals
 // (-1/sigma)^n He_n(t) exp(-t^2/2) with the probabilists' Hermite polynomials.
+#include <type_traits>
+
 #include "h6_internal.h"
 
 namespace h6 {
@@ -129,9 +131,16 @@ __device__ __forceinline__ void row_coefs(const RhsCoef& a, const S (&gy)[5], co
   }
 }
 
-// Sources of the row kernel.  factor(s, axis, i, g): derivatives 0..4 of the
-// axis factor of source s at the i-th unknown; amp(s): its coefficient (zero
-// past the last source, whose factor is then source 0's).
+// The same for the Neumann x faces: at the end nodes of the row F gets
+// +- (C[3]_s (d X)_s + C[4]_s (d3 X)_s), + on the low face.
+template <typename S>
+__device__ __forceinline__ void xface_coefs(const RhsCoef& a, const S (&gy)[5], const S (&gz)[5], double2& C3,
+                                            double2& C4) {
+  const S p00 = fm(gy[0], gz[0]), lap = fa(fm(gy[2], gz[0]), fm(gy[0], gz[2]));
+  C3 = ca(cmf(a.nN1, p00), cmf(a.nNm, lap));
+  C4 = cmf(a.nN3, p00);
+}
+
 // coordinate of node q, rounded before the centre is subtracted (as everywhere
 // else; a fused multiply-add would shift every t by up to an ulp of the node)
 __device__ __forceinline__ double node_coord(int q, double h) {
@@ -140,6 +149,9 @@ __device__ __forceinline__ double node_coord(int q, double h) {
   return x;
 }
 
+// Sources of the row kernel.  factor(s, axis, i, g): derivatives 0..4 of the
+// axis factor of source s at the i-th unknown; amp(s): its coefficient (zero
+// past the last source, whose factor is then source 0's).
 struct GaussSrc {
   using S = double;
   const RhsArgs& a;
@@ -179,17 +191,24 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // times i.  Tile row 4 e + g is part e & 1 of grid row 2 g + (e >> 1), so a
 // lane ends with two whole complex values.  More than 4 NQ sources: the rest
 // is added by further passes over the wave's own rows.
+// The terms of Neumann x faces go into the tiles that hold the end nodes as two
+// more orders; a kernel of its own for them cost every such call 2 to 5 us and 25 us
+// with 64 sources (31^3: 64 -> 39).
 // The pass is bound by the store of F: 256 x 258 x 258, eight Gaussians, takes
-// 64 us (4.3 TB/s of stores), against 970 us with every node forming 22
-// derivative products per source from three exponentials.  Errors against 80-bit
-// arithmetic over 32 face patterns, source counts and wavenumbers: 3.5e-16 on
-// average (3.6e-16 that way), 1.6e-16 for tables (1.7e-16).
+// 62 us (4.4 TB/s of stores), against 970 us with every node forming 22
+// derivative products per source from three exponentials.  Three waves per SIMD
+// (few registers short of it by default: 128 x 128 x 128, 64 Gaussians, Neumann x
+// 182 -> 143 us), two where tables with Neumann x faces would spill.  Errors against
+// 80-bit arithmetic over 32 face patterns, source counts and wavenumbers: 3.5e-16 on
+// average (3.6e-16 node by node), 1.6e-16 for tables (1.7e-16).
 constexpr int kRhsTiles = 2, kRhsRows = 8 * kRhsTiles;      // grid rows per wave
 
-template <typename Src, int NQ>
+// XF: Neumann x faces; the tiles that hold an end node take their two orders more.
+template <typename Src, int NQ, bool XF>
 __device__ __forceinline__ void rhs_rows(const RhsCoef& a, const Src& src, double2* __restrict__ F) {
   using S = typename Src::S;
   constexpr bool kCplx = sizeof(S) == 16;
+  constexpr int NO = XF ? 5 : 3;
   const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
   const int nx = a.dims[0], ny = a.dims[1], nrows = ny * a.dims[2];
   const int row0 = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * kRhsRows;
@@ -197,7 +216,7 @@ __device__ __forceinline__ void rhs_rows(const RhsCoef& a, const Src& src, doubl
   // this lane's A rows: tile row c16 = part of grid row
   const int sub = 2 * (c16 & 3) + (c16 >> 3), part = (c16 >> 2) & 1;
   for (int s0 = 0; s0 == 0 || s0 < src.count(); s0 += 4 * NQ) {
-    double2 C[kRhsTiles][NQ][3];
+    double2 C[kRhsTiles][NQ][NO];
 #pragma unroll
     for (int t = 0; t < kRhsTiles; ++t) {
       const int row = min(row0 + 8 * t + sub, nrows - 1);
@@ -208,10 +227,14 @@ __device__ __forceinline__ void rhs_rows(const RhsCoef& a, const Src& src, doubl
         S gy[5], gz[5];
         src.factor(sidx, 1, j, gy);
         src.factor(sidx, 2, l, gz);
-        row_coefs<S>(a, gy, gz, j + a.qlo[1], l + a.qlo[2], C[t][q]);
+        double2 c3[3];
+        row_coefs<S>(a, gy, gz, j + a.qlo[1], l + a.qlo[2], c3);
+#pragma unroll
+        for (int o = 0; o < 3; ++o) C[t][q][o] = c3[o];
+        if constexpr (XF) xface_coefs<S>(a, gy, gz, C[t][q][3], C[t][q][4]);
         const double2 am = src.amp(sidx);
 #pragma unroll
-        for (int o = 0; o < 3; ++o) {
+        for (int o = 0; o < NO; ++o) {
           const double2 v = cm(am, C[t][q][o]);
           // A value of this lane's part against a real factor, and against an imaginary one
           C[t][q][o] = make_double2(part ? v.y : v.x, part ? v.x : -v.y);
@@ -224,7 +247,8 @@ __device__ __forceinline__ void rhs_rows(const RhsCoef& a, const Src& src, doubl
 #pragma unroll
       for (int t = 0; t < kRhsTiles; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
       S g0[NQ];
-      auto add = [&](const double2 (&c)[NQ][3], int q, int o, S gv, d4& v) {
+      const double end = x == 0 ? 1.0 : x == nx - 1 ? -1.0 : 0.0;
+      auto add = [&](const double2 (&c)[NQ][NO], int q, int o, S gv, d4& v) {
         if constexpr (kCplx) {
           v = __builtin_amdgcn_mfma_f64_16x16x4f64(c[q][o].x, gv.x, v, 0, 0, 0);
           v = __builtin_amdgcn_mfma_f64_16x16x4f64(c[q][o].y, gv.y, v, 0, 0, 0);
@@ -232,8 +256,9 @@ __device__ __forceinline__ void rhs_rows(const RhsCoef& a, const Src& src, doubl
           v = __builtin_amdgcn_mfma_f64_16x16x4f64(c[q][o].x, gv, v, 0, 0, 0);
         }
       };
-      // orders 4 and 2 of every source first: their products are h^2 smaller, and
-      // added one by one to the large ones each would round the sum once more
+      // orders 4 and 2 of every source (and the face's 3 and 1) first: their products are
+      // h or h^2 smaller, and added one by one to the large ones each would round the sum
+      // once more
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
         S gx[5];
@@ -243,6 +268,19 @@ __device__ __forceinline__ void rhs_rows(const RhsCoef& a, const Src& src, doubl
         for (int o = 2; o > 0; --o)
 #pragma unroll
           for (int t = 0; t < kRhsTiles; ++t) add(C[t], q, o, gx[2 * o], acc[t]);
+        if constexpr (XF)
+          if (x0 == 0 || x0 + 16 >= nx) {
+            S g1{}, g3{};
+            if (end != 0.0) {
+              g1 = fs(gx[1], end);
+              g3 = fs(gx[3], end);
+            }
+#pragma unroll
+            for (int t = 0; t < kRhsTiles; ++t) {
+              add(C[t], q, 4, g3, acc[t]);
+              add(C[t], q, 3, g1, acc[t]);
+            }
+          }
       }
 #pragma unroll
       for (int q = 0; q < NQ; ++q)
@@ -265,54 +303,19 @@ __device__ __forceinline__ void rhs_rows(const RhsCoef& a, const Src& src, doubl
   }
 }
 
-// terms of the Neumann x faces, F +- R_N on the two planes of end nodes
-template <typename Src>
-__device__ __forceinline__ void rhs_xface(const RhsCoef& a, const Src& src, double2* __restrict__ F) {
-  using S = typename Src::S;
-  const int nx = a.dims[0], ny = a.dims[1], nrows = ny * a.dims[2];
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= 2 * nrows) return;
-  const int side = idx >= nrows, row = idx - side * nrows, i = side ? nx - 1 : 0;
-  double2 sum = make_double2(0.0, 0.0);
-  for (int s = 0; s < src.count(); ++s) {
-    S gx[5], gy[5], gz[5];
-    src.factor(s, 0, i, gx);
-    src.factor(s, 1, row % ny, gy);
-    src.factor(s, 2, row / ny, gz);
-    const S p00 = fm(gy[0], gz[0]), lap = fa(fm(gy[2], gz[0]), fm(gy[0], gz[2]));
-    const double2 r = ca(ca(cmf(a.nN1, fm(gx[1], p00)), cmf(a.nN3, fm(gx[3], p00))), cmf(a.nNm, fm(gx[1], lap)));
-    sum = ca(sum, cm(src.amp(s), r));
-  }
-  double2* o = F + size_t(row) * nx + i;
-  *o = ca(*o, cs(sum, side ? -1.0 : 1.0));
+template <int NQ, bool XF>
+__global__ __launch_bounds__(256, 3) void rhs_kernel(RhsArgs a, double2* __restrict__ F) {
+  const GaussSrc src{a};
+  rhs_rows<GaussSrc, NQ, XF>(a.c, src, F);
 }
 
-template <int NQ>
-__global__ __launch_bounds__(256) void rhs_kernel(RhsArgs a, double2* __restrict__ F) {
-  const GaussSrc src{a};
-  rhs_rows<GaussSrc, NQ>(a.c, src, F);
-}
-__global__ __launch_bounds__(256) void rhs_xface_kernel(RhsArgs a, double2* __restrict__ F) {
-  const GaussSrc src{a};
-  rhs_xface(a.c, src, F);
-}
-
-template <int NQ>
-__global__ __launch_bounds__(256) void rhs_separable_kernel(RhsCoef a, int nterms, const double2* __restrict__ coef,
+template <int NQ, bool XF>
+__global__ __launch_bounds__(256, XF && NQ == 2 ? 2 : 3) void rhs_separable_kernel(RhsCoef a, int nterms, const double2* __restrict__ coef,
                                                             const double2* __restrict__ tx,
                                                             const double2* __restrict__ ty,
                                                             const double2* __restrict__ tz, double2* __restrict__ F) {
   const TableSrc src{a, nterms, coef, {tx, ty, tz}};
-  rhs_rows<TableSrc, NQ>(a, src, F);
-}
-__global__ __launch_bounds__(256) void rhs_separable_xface_kernel(RhsCoef a, int nterms,
-                                                                  const double2* __restrict__ coef,
-                                                                  const double2* __restrict__ tx,
-                                                                  const double2* __restrict__ ty,
-                                                                  const double2* __restrict__ tz,
-                                                                  double2* __restrict__ F) {
-  const TableSrc src{a, nterms, coef, {tx, ty, tz}};
-  rhs_xface(a, src, F);
+  rhs_rows<TableSrc, NQ, XF>(a, src, F);
 }
 
 // Dirichlet data g (n'x x n'y, x fastest) on a z face: Fp -= G g on the
@@ -397,18 +400,24 @@ RhsCoef rhs_coef(h6_plan P) {
   return a;
 }
 
-// launch shapes of the row kernels (four waves of kRhsRows rows) and of the x-face planes (Neumann x pair)
-struct RhsGrid {
-  dim3 rows;
-  unsigned xface;
-};
-RhsGrid rhs_grid(h6_plan P) {
+// launch of the row kernels: four waves of kRhsRows rows per workgroup; go(NQ, XF, grid)
+template <typename F>
+void rhs_launch(h6_plan P, int count, F&& go) {
   const size_t nrows = size_t(P->dims[1]) * P->dims[2];
   const unsigned wg = unsigned((nrows + 4 * kRhsRows - 1) / (4 * kRhsRows));
   // small grids: the x tiles of a row group are shared out until there are
   // about two waves per SIMD (each share forms the row constants again)
   const unsigned tiles = unsigned(P->dims[0] + 15) / 16, split = (512 + wg - 1) / wg;
-  return RhsGrid{dim3(wg, split < tiles ? split : tiles), P->xmirror ? unsigned((2 * nrows + 255) / 256) : 0u};
+  const dim3 grid(wg, split < tiles ? split : tiles);
+  constexpr std::integral_constant<int, 1> one{};
+  constexpr std::integral_constant<int, 2> two{};
+  if (P->xmirror) {
+    if (count <= 4) go(one, std::true_type{}, grid);
+    else go(two, std::true_type{}, grid);
+  } else {
+    if (count <= 4) go(one, std::false_type{}, grid);
+    else go(two, std::false_type{}, grid);
+  }
 }
 
 // Neumann data on face plane (axis ax, side): beta = sum_s coef[s] T1_s(t1) T2_s(t2)
@@ -465,12 +474,9 @@ hipError_t launch_rhs(h6_plan P, int nsrc, const double* centres, const double* 
   }
   hipEvent_t ev;
   timing_begin(P, KC_RHS, s, &ev);
-  const RhsGrid gr = rhs_grid(P);
-  if (nsrc <= 4)
-    hipLaunchKernelGGL(rhs_kernel<1>, gr.rows, dim3(256), 0, s, a, F);
-  else
-    hipLaunchKernelGGL(rhs_kernel<2>, gr.rows, dim3(256), 0, s, a, F);
-  if (gr.xface) hipLaunchKernelGGL(rhs_xface_kernel, dim3(gr.xface), dim3(256), 0, s, a, F);
+  rhs_launch(P, nsrc, [&](auto NQ, auto XF, dim3 grid) {
+    hipLaunchKernelGGL((rhs_kernel<NQ(), XF()>), grid, dim3(256), 0, s, a, F);
+  });
   timing_end(P, KC_RHS, s, ev, double(P->N) * sizeof(double2));
   return hipGetLastError();
 }
@@ -503,15 +509,11 @@ hipError_t launch_rhs_separable(h6_plan P, int nterms, const double* coef, const
   if (e != hipSuccess) return e;
   hipEvent_t ev;
   timing_begin(P, KC_RHS, s, &ev);
-  const RhsGrid gr = rhs_grid(P);
   const RhsCoef a = rhs_coef(P);
-  if (nterms <= 4)
-    hipLaunchKernelGGL(rhs_separable_kernel<1>, gr.rows, dim3(256), 0, s, a, nterms, dcoef, dtab[0], dtab[1], dtab[2], F);
-  else
-    hipLaunchKernelGGL(rhs_separable_kernel<2>, gr.rows, dim3(256), 0, s, a, nterms, dcoef, dtab[0], dtab[1], dtab[2], F);
-  if (gr.xface)
-    hipLaunchKernelGGL(rhs_separable_xface_kernel, dim3(gr.xface), dim3(256), 0, s, a, nterms, dcoef, dtab[0], dtab[1],
+  rhs_launch(P, nterms, [&](auto NQ, auto XF, dim3 grid) {
+    hipLaunchKernelGGL((rhs_separable_kernel<NQ(), XF()>), grid, dim3(256), 0, s, a, nterms, dcoef, dtab[0], dtab[1],
                        dtab[2], F);
+  });
   timing_end(P, KC_RHS, s, ev, double(P->N) * sizeof(double2));
   e = hipGetLastError();
   if (e != hipSuccess) return e;
