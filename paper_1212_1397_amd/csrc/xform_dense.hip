@@ -22,8 +22,9 @@
 // 32 b .. 32 b + 31) of 32 lines (x) or 64 columns (y), folding the line
 // halves into u and v as it stages K chunks in LDS.  We and Wo are stored
 // zero-padded to [Hm][Hk] (Hm a multiple of 32, Hk of the K chunk), so
-// operand reads of them need no bounds checks.  (These K-chunked kernels take only
-// the lines too long for the slab kernels below.)
+// operand reads of them need no bounds checks.  (These K-chunked kernels take the
+// lines too long for the slab kernels below and long lines that are few, see
+// slab_shape.)
 #include <algorithm>
 
 #include "h6_internal.h"
@@ -693,14 +694,23 @@ struct SlabShape {
   int waves = 0, rounds = 0;
 };
 
-template <typename R> SlabShape slab_shape(int L, bool x) {
+// Few long lines: a workgroup forms a line's outputs 256 at a time (a round of its waves),
+// the K-chunked kernels 64 each in workgroups of their own, so while CUs are idle the
+// slab kernels lose from the second round on in complex128 and along complex64 x lines
+// of a single slab, from the fourth along complex64 y.  Slab against K-chunked: complex128
+// x, 516 values, 128 / 1024 / 4096 lines 43 / 50 / 58 us against 33 / 43 / 97; y, 632
+// values, 128 / 1024 / 2048 / 4096 columns 71 / 72 / 75 / 82 against 49 / 58 / 71 / 126;
+// complex64 y, 1264 values, 128 / 1024 / 2048 columns 121 / 120 / 124 against 81 / 94 / 169.
+template <typename R> SlabShape slab_shape(int L, bool x, int workgroups) {
   const int H = L - L / 2, units = (H - slab_border(H) + 15) / 16;
   size_t lds = 2 * size_t(kSlabRows) * slab_stride<R>(H) * sizeof(R);
   if (x) lds = std::max(lds, size_t(kSlabLines) * slab_out_stride<R>(L) * 2 * sizeof(R));
   SlabShape s;
   s.rounds = (units + 7) / 8;
   s.waves = std::max((units + s.rounds - 1) / s.rounds, 4);
-  s.lds = lds <= 159 * 1024 && !(x && s.rounds > 2) ? lds : 0;
+  const bool f64 = sizeof(R) == 8;
+  const bool few = workgroups < (x ? (f64 ? 256 : 2) : 128) && s.rounds > (x || f64 ? 1 : 3);
+  s.lds = lds <= 159 * 1024 && !(x && s.rounds > 2) && !few ? lds : 0;
   return s;
 }
 
@@ -715,9 +725,10 @@ hipError_t launch_dense_x(const AxisXform& X, bool inverse, const Tin* in, Tout*
                           hipStream_t s, const int* skip) {
   const R* W = static_cast<const R*>(X.wmat) + (inverse ? 2 * size_t(X.Hm) * X.Hk : 0);
   const int H = X.L - X.L / 2;
-  const SlabShape sh = slab_shape<R>(X.L, true);
+  const int slabs = (nlines + kSlabLines - 1) / kSlabLines;
+  const SlabShape sh = slab_shape<R>(X.L, true, slabs);
   if (sh.lds) {
-    const dim3 grid((nlines + kSlabLines - 1) / kSlabLines), block(64 * sh.waves);
+    const dim3 grid(slabs), block(64 * sh.waves);
     auto go = [&](auto kern) {
       hipLaunchKernelGGL(kern, grid, block, sh.lds, s, in, out, W, X.Hm, X.Hk, X.L, nlines, div_magic(H),
                          div_magic(X.L), acc, skip);
@@ -737,9 +748,10 @@ hipError_t launch_dense_y(const AxisXform& Y, bool inverse, const T2* in, T2* ou
                           hipStream_t s, const int* skip) {
   const R* W = static_cast<const R*>(Y.wmat) + (inverse ? 2 * size_t(Y.Hm) * Y.Hk : 0);
   const int ncols = 2 * nx, H = Y.L - Y.L / 2;
-  const SlabShape sh = slab_shape<R>(Y.L, false);
+  const int slabs = (nx + kSlabLines - 1) / kSlabLines * nz;
+  const SlabShape sh = slab_shape<R>(Y.L, false, slabs);
   if (sh.lds) {
-    const dim3 grid(unsigned((nx + kSlabLines - 1) / kSlabLines) * nz), block(64 * sh.waves);
+    const dim3 grid(slabs), block(64 * sh.waves);
     hipLaunchKernelGGL((slab_y_kernel<R>), grid, block, sh.lds, s, reinterpret_cast<const R*>(in),
                        reinterpret_cast<R*>(out), W, Y.Hm, Y.Hk, Y.L, nx, skip);
     return hipGetLastError();
