@@ -280,7 +280,10 @@ h6_status helmholtz6_set_graphs(h6_plan plan, int enable);
  * and the dense transform else; with the environment variable
  * H6_DENSE_TRANSFORMS set at setup only the dense transform is built.  With
  * cache_path != NULL the choice is read from, or appended to, that text file
- * (one line per grid shape, precision and device).  Synchronous. */
+ * (one line per grid shape, x and y basis, precision and device).  Lines of
+ * earlier versions, which do not name the bases (axes=..), are taken as they
+ * stand by every plan of the shape and precision; delete them to have such
+ * grids timed with the variants added since.  Synchronous. */
 h6_status helmholtz6_autotune(h6_plan plan, const char* cache_path, void* hip_stream);
 
 /* Per-kernel timing: when enabled, the library records HIP events around

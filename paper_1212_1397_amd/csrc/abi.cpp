@@ -691,6 +691,12 @@ h6_status autotune(h6_plan P, const char* cache_path, hipStream_t s) {
   char key[512];
   std::snprintf(key, sizeof key, "h6tune3 %s %d %d %d %d", devname, P->dims[0], P->dims[1], P->dims[2],
                 P->p.precision);
+  // The transforms a plan can take depend on M = n + 1 and the basis, which the unknown
+  // counts do not tell apart (255: M = 256 sine or 254 cosine): lines end in both.  Lines
+  // without them (earlier versions') hold for every plan of the counts, as they stand.
+  char axes[64];
+  std::snprintf(axes, sizeof axes, "axes=%c%d,%c%d", P->ax[0].neumann ? 'N' : 'D', P->ax[0].M,
+                P->ax[1].neumann ? 'N' : 'D', P->ax[1].M);
   const bool can_x = P->ax[0].rader_mem != nullptr, can_y = P->ax[1].rader_mem != nullptr;
   // transform variant code of the cache (0 dense, 1 Rader, 2 Bluestein, 3 power-of-two FFT) -> the variants this plan has
   auto fast_code = [&](int ax, int code) {
@@ -702,23 +708,26 @@ h6_status autotune(h6_plan P, const char* cache_path, hipStream_t s) {
   if (cache_path) {
     if (FILE* f = std::fopen(cache_path, "r")) {
       char line[600];
-      while (std::fgets(line, sizeof line, f)) {
-        int tz = 0, xf = 0, yf = 0, xl = 0, yl = 0;
+      int found = 0;                // 1: a line without axes, 2: one of the plan's axes
+      while (found < 2 && std::fgets(line, sizeof line, f)) {
+        int tz = 0, xf = 0, yf = 0, xl = 0, yl = 0, end = 0;
         const size_t kl = std::strlen(key);
-        if (std::strncmp(line, key, kl) == 0 && line[kl] == ' ' &&
-            std::sscanf(line + kl, " tz=%d xfast=%d yfast=%d xlines=%d ylines=%d", &tz, &xf, &yf, &xl,
-                        &yl) == 5 &&
-            stencil_tz_ok(tz) && rader_lines_ok(0, xl) && rader_lines_ok(1, yl)) {
-          std::fclose(f);
-          P->stencil_tz = tz;
-          P->ax[0].fast = fast_code(0, xf);
-          P->ax[1].fast = fast_code(1, yf);
-          P->ax[0].lines = xl;
-          P->ax[1].lines = yl;
-          return H6_OK;
-        }
+        if (std::strncmp(line, key, kl) != 0 || line[kl] != ' ' ||
+            std::sscanf(line + kl, " tz=%d xfast=%d yfast=%d xlines=%d ylines=%d%n", &tz, &xf, &yf, &xl, &yl, &end) != 5 ||
+            !stencil_tz_ok(tz) || !rader_lines_ok(0, xl) || !rader_lines_ok(1, yl))
+          continue;
+        char of[64] = "";
+        const bool named = std::sscanf(line + kl + end, " %63s", of) == 1 && std::strncmp(of, "axes=", 5) == 0;
+        if (named ? std::strcmp(of, axes) != 0 : found > 0) continue;
+        found = named ? 2 : 1;
+        P->stencil_tz = tz;
+        P->ax[0].fast = fast_code(0, xf);
+        P->ax[1].fast = fast_code(1, yf);
+        P->ax[0].lines = xl;
+        P->ax[1].lines = yl;
       }
       std::fclose(f);
+      if (found) return H6_OK;
     }
   }
   void *a = nullptr, *b = nullptr;
@@ -798,8 +807,8 @@ h6_status autotune(h6_plan P, const char* cache_path, hipStream_t s) {
   }
   if (cache_path) {
     if (FILE* f = std::fopen(cache_path, "a")) {
-      std::fprintf(f, "%s tz=%d xfast=%d yfast=%d xlines=%d ylines=%d\n", key, P->stencil_tz,
-                   int(P->ax[0].fast), int(P->ax[1].fast), P->ax[0].lines, P->ax[1].lines);
+      std::fprintf(f, "%s tz=%d xfast=%d yfast=%d xlines=%d ylines=%d %s\n", key, P->stencil_tz,
+                   int(P->ax[0].fast), int(P->ax[1].fast), P->ax[0].lines, P->ax[1].lines, axes);
       std::fclose(f);
     }
   }
