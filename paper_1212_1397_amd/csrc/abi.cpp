@@ -714,7 +714,7 @@ h6_status autotune(h6_plan P, const char* cache_path, hipStream_t s) {
         const size_t kl = std::strlen(key);
         if (std::strncmp(line, key, kl) != 0 || line[kl] != ' ' ||
             std::sscanf(line + kl, " tz=%d xfast=%d yfast=%d xlines=%d ylines=%d%n", &tz, &xf, &yf, &xl, &yl, &end) != 5 ||
-            !stencil_tz_ok(tz) || !rader_lines_ok(0, xl) || !rader_lines_ok(1, yl))
+            !stencil_tz_ok(P, tz) || !rader_lines_ok(0, xl) || !rader_lines_ok(1, yl))
           continue;
         char of[64] = "";
         const bool named = std::sscanf(line + kl + end, " %63s", of) == 1 && std::strncmp(of, "axes=", 5) == 0;
@@ -766,6 +766,7 @@ h6_status autotune(h6_plan P, const char* cache_path, hipStream_t s) {
   int best_tz = 16;
   double best_ms = 1e30;
   for (int tz : {2, 4, 8, 16, 32}) {
+    if (!stencil_tz_ok(P, tz)) continue;
     P->stencil_tz = tz;
     const double ms = time_it([&] { (void)launch_stencil(P, x, y, nullptr, nullptr, nullptr, s); });
     if (ms < best_ms) { best_ms = ms; best_tz = tz; }

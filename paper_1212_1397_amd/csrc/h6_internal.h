@@ -242,7 +242,7 @@ hipError_t launch_stencil_f32in(h6_plan P, const float2* x, double2* y, hipStrea
 int stencil_workgroups(h6_plan P);
 // tile width and z-chunk depth of an untuned plan
 void stencil_defaults(h6_plan P);
-bool stencil_tz_ok(int tz);
+bool stencil_tz_ok(h6_plan P, int tz);
 hipError_t launch_resid_f32out(h6_plan P, const double2* U, float2* r, const double2* F,
                                double* partials, int* nparts, hipStream_t s, double* fpartials = nullptr);
 // Dense (matrix-core) transforms along x / y with the axis' basis matrices

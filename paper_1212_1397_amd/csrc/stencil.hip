@@ -260,11 +260,16 @@ hipError_t launch_stencil_f32in(h6_plan P, const float2* x, double2* y, hipStrea
   return stencil_impl(P, x, y, static_cast<const double2*>(nullptr), nullptr, nullptr, s);
 }
 
-bool stencil_tz_ok(int tz) { return tz == 2 || tz == 4 || tz == 8 || tz == 16 || tz == 32; }
-
-int stencil_workgroups(h6_plan P) {
-  const int tx = P->stencil_tx, ty = 512 / tx, tz = P->stencil_tz;
+static int workgroups(h6_plan P, int tz) {
+  const int tx = P->stencil_tx, ty = 512 / tx;
   return ((P->dims[0] + tx - 1) / tx) * ((P->dims[1] + ty - 1) / ty) * ((P->dims[2] + tz - 1) / tz);
+}
+
+int stencil_workgroups(h6_plan P) { return workgroups(P, P->stencil_tz); }
+
+// the residual kernel keeps a partial sum per workgroup
+bool stencil_tz_ok(h6_plan P, int tz) {
+  return (tz == 2 || tz == 4 || tz == 8 || tz == 16 || tz == 32) && workgroups(P, tz) <= kMaxPartials;
 }
 
 // The tile is 32 wide where that wastes fewer lanes (n'x = 160: 26.5 against
