@@ -559,13 +559,14 @@ h6_status setup_impl(const h6_params* p, hipStream_t s, h6_plan* out, std::strin
     if (P->ax[a].M == kRaderM && !std::getenv("H6_DENSE_TRANSFORMS")) e = build_rader(P->ax[a], s);
     else if (bluestein_ok(P->ax[a].M) && P->ax[a].L <= 256 && !std::getenv("H6_DENSE_TRANSFORMS")) {
       e = build_bluestein(P->ax[a], s);
-      // Untuned default where the FFT length is nearly all signal (2M - 2 >= 15/16 P).
-      // P = 512 (M = 241 .. 255): the dense product, faster since its slab kernels and no
-      // less exact (apply_Pinv 254 x 254 x 160, chirp-z against dense: complex64 577 ->
-      // 381 us, complex128 1052 -> 644).  The chirp-z path stays on axes of fewer lines
-      // than one slab (254 x 2 x 2: 39 against 27 us) and for P = 256 (M = 121 .. 129;
-      // 128 x 130 x 130 complex64 110 against 84 us): there what untuned plans return is
-      // pinned bit for bit, and plans that care are autotuned, which times both.
+      // Untuned plans used to take chirp-z where the FFT length is nearly all signal
+      // (2M - 2 >= 15/16 P).  With slab kernels the dense product is faster for every odd
+      // M and closer to exact (254 x 40 x 3: a fifth to a quarter of chirp-z's error), so
+      // P = 512 (M = 241 .. 255) now takes it (apply_Pinv 254 x 254 x 160, chirp-z against
+      // dense: complex64 577 -> 381 us, complex128 1052 -> 644).  Not for speed but so
+      // that untuned results keep the bits that they had, chirp-z stays for P = 256 (M = 121
+      // .. 129; 128 x 130 x 130 complex64 110 against 84 us) and on axes of fewer lines
+      // than one slab (254 x 2 x 2: 39 against 27 us); autotuned plans time both.
       const int M = P->ax[a].M, lines = P->dims[1 - a] * P->dims[2];
       if (e == hipSuccess && 16 * (2 * M - 2) >= 15 * bluestein_length(M) && (bluestein_length(M) == 256 || lines < 16))
         P->ax[a].fast = 2;

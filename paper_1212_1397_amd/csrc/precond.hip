@@ -9,10 +9,11 @@
 // W_qm = cos(pi q m / M) (q, m = 0..M); W^{-1} = (2/M) W^T and
 // (2/M) C W^T C (C = diag(1/2, 1, .., 1, 1/2)) respectively.
 //
-// Steps 1, 2, 4, 5 use an FFT path for M = 257 (xform_rader.hip) and M = 64 .. 512
-// a power of two (xform_fft.hip), the dense basis-matrix products on the matrix
-// cores otherwise (xform_dense.hip), and chirp-z for odd M (xform_bluestein.hip)
-// where the autotuner finds it faster.  Compute type R is double (FP64 plans) or float (mixed
+// Steps 1, 2, 4, 5 take the path that each axis holds (AxisXform::fast): Rader FFT
+// (xform_rader.hip), chirp-z (xform_bluestein.hip), power-of-two FFT (xform_fft.hip)
+// or the dense basis-matrix products on the matrix cores (xform_dense.hip).  setup_impl
+// (abi.cpp) states which one an untuned plan holds and why; the autotuner times those
+// that the axis' M allows.  Compute type R is double (FP64 plans) or float (mixed
 // plans, complex64 intermediates); the input r and output z are complex128 in
 // both.
 #include <mutex>
@@ -294,9 +295,9 @@ hipError_t pinv_impl(h6_plan P, const Tin* r, Tout* z, hipStream_t s, int part, 
     const T2* cst = static_cast<const T2*>(P->d_cstart);
     // neighbouring mode groups share 128-byte lines where a plane is not a
     // multiple of the group, and DRAM pages anyway: vectors beyond the caches
-    // keep them under one L2 (255 x 255 x 256: 189 -> 148 us in complex128, 86 ->
-    // 70 in complex64; 511 x 511 x 512 1420 -> 1042; 256 x 258 x 258 complex64 68 ->
-    // 65).  Cache-resident ones do not (127 x 127 x 128 complex64 14 -> 16 us).
+    // keep them under one L2 (255 x 255 x 256: 175 -> 145 us in complex128, 83 -> 68 in
+    // complex64; 511 x 511 x 512 1341 -> 1049, 744 -> 543; 256 x 258 x 258 150 -> 130, 67
+    // -> 62).  Cache-resident ones do not (127 x 127 x 128 complex64 14 -> 16 us).
     const int remap = P->N * sizeof(T2) > (size_t(48) << 20);
     auto go = [&](auto kern, int lanes, int threads = 512) {
       hipLaunchKernelGGL(kern, dim3((nx * ny + lanes - 1) / lanes), dim3(threads), 0, s, w1, w0, cst,

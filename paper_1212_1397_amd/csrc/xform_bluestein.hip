@@ -374,8 +374,9 @@ void launch_b(bool neumann, bool inv, const Tin* in, Tout* out, int nlines, int 
 
 }  // namespace
 
-// lines per workgroup: 4 along x (16 in complex64 with P = 256); along y 16 (complex64, P = 256), 8 (complex64 with P = 512 or
-// complex128 with P = 256), 4 (complex128, P = 512): LDS per workgroup 17-35 KB
+// lines per workgroup: 4 along x (16 in complex64 with P = 256); along y 16 (complex64,
+// P = 256), 8 (complex64 with P = 512 or complex128 with P = 256), 4 (complex128, P = 512):
+// LDS per workgroup 17-47 KB, of which the tables of P = 256 take 6 (complex64) or 12 KB
 template <typename R, typename Tin, typename Tout>
 hipError_t launch_bluestein_x(bool neumann, bool inverse, const Tin* in, Tout* out, int nlines, int L,
                               const BluesteinTables& tab, hipStream_t s, int accumulate, const int* skip) {
