@@ -195,7 +195,7 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // more orders; a kernel of its own for them cost every such call 2 to 5 us and 25 us
 // with 64 sources (31^3: 64 -> 39).
 // The pass is bound by the store of F: 256 x 258 x 258, eight Gaussians, takes
-// 62 us (4.4 TB/s of stores), against 970 us with every node forming 22
+// 69 us (4.0 TB/s of stores), against 970 us with every node forming 22
 // derivative products per source from three exponentials.  Three waves per SIMD
 // (few registers short of it by default: 128 x 128 x 128, 64 Gaussians, Neumann x
 // 182 -> 143 us), two where tables with Neumann x faces would spill.  Errors against
@@ -310,10 +310,9 @@ __global__ __launch_bounds__(256, 3) void rhs_kernel(RhsArgs a, double2* __restr
 }
 
 template <int NQ, bool XF>
-__global__ __launch_bounds__(256, XF && NQ == 2 ? 2 : 3) void rhs_separable_kernel(RhsCoef a, int nterms, const double2* __restrict__ coef,
-                                                            const double2* __restrict__ tx,
-                                                            const double2* __restrict__ ty,
-                                                            const double2* __restrict__ tz, double2* __restrict__ F) {
+__global__ __launch_bounds__(256, XF && NQ == 2 ? 2 : 3) void rhs_separable_kernel(
+    RhsCoef a, int nterms, const double2* __restrict__ coef, const double2* __restrict__ tx,
+    const double2* __restrict__ ty, const double2* __restrict__ tz, double2* __restrict__ F) {
   const TableSrc src{a, nterms, coef, {tx, ty, tz}};
   rhs_rows<TableSrc, NQ, XF>(a, src, F);
 }
