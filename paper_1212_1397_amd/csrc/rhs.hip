@@ -198,7 +198,8 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // 69 us (4.0 TB/s of stores), against 970 us with every node forming 22
 // derivative products per source from three exponentials.  Three waves per SIMD
 // (few registers short of it by default: 128 x 128 x 128, 64 Gaussians, Neumann x
-// 182 -> 143 us), two where tables with Neumann x faces would spill.  Errors against
+// 182 -> 143 us), two for tables of more than four terms (256 x 258 x 256, six terms:
+// three 112 us, two 95).  Errors against
 // 80-bit arithmetic over 32 face patterns, source counts and wavenumbers: 3.5e-16 on
 // average (3.6e-16 node by node), 1.6e-16 for tables (1.7e-16).
 constexpr int kRhsTiles = 2, kRhsRows = 8 * kRhsTiles;      // grid rows per wave
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(256, 3) void rhs_kernel(RhsArgs a, double2* __restr
 }
 
 template <int NQ, bool XF>
-__global__ __launch_bounds__(256, XF && NQ == 2 ? 2 : 3) void rhs_separable_kernel(
+__global__ __launch_bounds__(256, NQ == 2 ? 2 : 3) void rhs_separable_kernel(
     RhsCoef a, int nterms, const double2* __restrict__ coef, const double2* __restrict__ tx,
     const double2* __restrict__ ty, const double2* __restrict__ tz, double2* __restrict__ F) {
   const TableSrc src{a, nterms, coef, {tx, ty, tz}};
