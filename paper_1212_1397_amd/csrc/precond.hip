@@ -312,7 +312,8 @@ hipError_t pinv_impl(h6_plan P, const Tin* r, Tout* z, hipStream_t s, int part, 
       else go(tridiag_z_kernel<R, kL, 8, 9, kPer>, kL, 8 * kL);
     } else if (segs == 16) {
       if constexpr (sizeof(R) == 4) {      // (complex64 only, see z_segments)
-        if (nz <= 16 * 9) go(tridiag_z_kernel<R, 32, 16, 9, 1>, 32);
+        if (nz <= 16 * 5) go(tridiag_z_kernel<R, 32, 16, 5, 1>, 32);
+        else if (nz <= 16 * 9) go(tridiag_z_kernel<R, 32, 16, 9, 1>, 32);
         else go(tridiag_z_kernel<R, 32, 16, 17, 1>, 32);
       }
     } else {

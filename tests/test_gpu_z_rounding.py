@@ -36,3 +36,18 @@ def test_short_lines_no_less_exact_than_16_segments(n, code, kh):
     err = (total / 10) ** 0.5
     print(f"{n} {code} {kh}: {err:.3e} (limit {LIMIT[n, code, kh]:.3e})", flush=True)
     assert err <= 1.1 * LIMIT[n, code, kh]
+
+
+@pytest.mark.parametrize("nz", [73, 79, 80, 81, 144, 145, 272, 273])
+def test_rows_per_thread_of_16_segments(nz):
+    """complex64 lines beyond 72 planes: five, nine or seventeen rows a thread, 32 segments
+    from 273 on; the bound of the other complex64 parity tests."""
+    from paper_1212_1397_amd import helmholtz6 as h6
+    for bc, n3 in (("DDNNDD", nz), ("DDNNSS", nz - 2)):
+        prob = oracle.Problem((11, 5, n3), 1.0 / 12, 6.0 + 0.3j, tuple(bc))
+        x = random_field(prob.shape, nz)
+        plan = h6.Plan(prob.n, prob.h, prob.k, bc, precision="mixed")
+        z = plan.apply_Pinv(torch.from_numpy(x).cuda()).cpu().numpy()
+        plan.close()
+        ref = oracle.apply_Pinv(prob, x)
+        assert np.abs(z - ref).max() <= 5e-5 * np.abs(ref).max()
