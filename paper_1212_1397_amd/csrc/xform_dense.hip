@@ -23,8 +23,8 @@
 // halves into u and v as it stages K chunks in LDS.  We and Wo are stored
 // zero-padded to [Hm][Hk] (Hm a multiple of 32, Hk of the K chunk), so
 // operand reads of them need no bounds checks.  (These K-chunked kernels take the
-// lines too long for the slab kernels below and long lines that are few, see
-// slab_shape.)
+// lines too long for the slab kernels below, long lines that are few and short x
+// lines, see slab_shape.)
 #include <algorithm>
 
 #include "h6_internal.h"
@@ -701,6 +701,15 @@ struct SlabShape {
 // x, 516 values, 128 / 1024 / 4096 lines 43 / 50 / 58 us against 33 / 43 / 97; y, 632
 // values, 128 / 1024 / 2048 / 4096 columns 71 / 72 / 75 / 82 against 49 / 58 / 71 / 126;
 // complex64 y, 1264 values, 128 / 1024 / 2048 columns 121 / 120 / 124 against 81 / 94 / 169.
+// Complex128 x lines also lose while the last CUs' second slabs are few (300 values, 275
+// slabs 43 against 36; 375 slabs 46 against 54).
+// Short lines: the K-chunked kernels read lines of up to 64 values once too, and up to 32
+// values are one unit, so one wave of a slab's workgroup has products to form.  Slabs are
+// no faster along x up to 32 values, and slower from 10^4 lines on (20 values, 131072
+// lines: complex128 26 against 23 us, complex64 22 against 19); along complex64 y from
+// about 1536 slabs on (20 values, 32768 columns 8.6 against 7.0 us; 33 to 64 values only
+// there, 48 values 14 against 12, 65536 columns 19 against 20); along complex128 y with
+// very many (40 values, 262144 columns 114 against 103).
 template <typename R> SlabShape slab_shape(int L, bool x, int workgroups) {
   const int H = L - L / 2, units = (H - slab_border(H) + 15) / 16;
   size_t lds = 2 * size_t(kSlabRows) * slab_stride<R>(H) * sizeof(R);
@@ -709,8 +718,12 @@ template <typename R> SlabShape slab_shape(int L, bool x, int workgroups) {
   s.rounds = (units + 7) / 8;
   s.waves = std::max((units + s.rounds - 1) / s.rounds, 4);
   const bool f64 = sizeof(R) == 8;
-  const bool few = workgroups < (x ? (f64 ? 256 : 2) : 128) && s.rounds > (x || f64 ? 1 : 3);
-  s.lds = lds <= 159 * 1024 && !(x && s.rounds > 2) && !few ? lds : 0;
+  const bool tail = x && f64 && workgroups > 256 && workgroups < 352;
+  const bool few = (workgroups < (x ? (f64 ? 256 : 2) : 128) || tail) && s.rounds > (x || f64 ? 1 : 3);
+  const bool brief = x     ? H <= 16
+                     : f64 ? H <= 32 && workgroups >= 12288
+                           : workgroups >= 1536 && H <= (workgroups < 3072 ? 32 : 16);
+  s.lds = lds <= 159 * 1024 && !(x && s.rounds > 2) && !few && !brief ? lds : 0;
   return s;
 }
 
