@@ -276,8 +276,8 @@ h6_status helmholtz6_set_graphs(h6_plan plan, int enable);
  * 255 the dense transform against the Bluestein (chirp-z) transform, for
  * n + 1 = 64, 128, 256 or 512 against a plain FFT) and keeps the fastest.
  * Untuned plans use Rader for n + 1 = 257, the FFT for those powers of two,
- * Bluestein for odd n + 1 = 121 .. 129 (241 .. 255 on axes of fewer than 16 lines)
- * and the dense transform else; with the environment variable
+ * Bluestein for odd n + 1 = 121 .. 129 (241 .. 255 on axes of fewer than 16 lines
+ * and along y where n'x < 6) and the dense transform else; with the environment variable
  * H6_DENSE_TRANSFORMS set at setup only the dense transform is built.  With
  * cache_path != NULL the choice is read from, or appended to, that text file
  * (one line per grid shape, x and y basis, precision and device).  Lines of

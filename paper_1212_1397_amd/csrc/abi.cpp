@@ -566,9 +566,13 @@ h6_status setup_impl(const h6_params* p, hipStream_t s, h6_plan* out, std::strin
       // dense: complex64 577 -> 381 us, complex128 1052 -> 644).  Not for speed but so
       // that untuned results keep the bits that they had, chirp-z stays for P = 256 (M = 121
       // .. 129; 128 x 130 x 130 complex64 110 against 84 us) and on axes of fewer lines
-      // than one slab (254 x 2 x 2: 39 against 27 us); autotuned plans time both.
+      // than one slab (254 x 2 x 2: 39 against 27 us); and for speed along y of grids under
+      // 6 wide, whose slabs of 16 columns of one plane stay nearly empty (4 x 254 x 500
+      // complex128 y 22 against 27 us).  Autotuned plans time both.
       const int M = P->ax[a].M, lines = P->dims[1 - a] * P->dims[2];
-      if (e == hipSuccess && 16 * (2 * M - 2) >= 15 * bluestein_length(M) && (bluestein_length(M) == 256 || lines < 16))
+      const bool nearly_empty = lines < 16 || (a == 1 && P->dims[0] < 6);
+      if (e == hipSuccess && 16 * (2 * M - 2) >= 15 * bluestein_length(M) &&
+          (bluestein_length(M) == 256 || nearly_empty))
         P->ax[a].fast = 2;
     }
     else if (fft_ok(P->ax[a].M) && !std::getenv("H6_DENSE_TRANSFORMS")) {

@@ -705,11 +705,13 @@ struct SlabShape {
 // slabs 43 against 36; 375 slabs 46 against 54).
 // Short lines: the K-chunked kernels read lines of up to 64 values once too, and up to 32
 // values are one unit, so one wave of a slab's workgroup has products to form.  Slabs are
-// no faster along x up to 32 values, and slower from 10^4 lines on (20 values, 131072
-// lines: complex128 26 against 23 us, complex64 22 against 19); along complex64 y from
+// no faster along x from 9 to 32 values, and slower from 10^4 lines on (20 values, 131072
+// lines: complex128 26 against 23 us, complex64 22 against 19; 8 values 19 against 21);
+// along complex128 y of 25 to 32 values from about 600 slabs on (32 x 32 x 500 10.5 against
+// 9.0, and the x passes after it 9.1 against 7.8); along complex64 y from
 // about 1536 slabs on (20 values, 32768 columns 8.6 against 7.0 us; 33 to 64 values only
-// there, 48 values 14 against 12, 65536 columns 19 against 20); along complex128 y with
-// very many (40 values, 262144 columns 114 against 103).
+// there, 48 values 14 against 12, 65536 columns 19 against 20); along longer complex128 y
+// with very many (40 values, 262144 columns 114 against 103).
 template <typename R> SlabShape slab_shape(int L, bool x, int workgroups) {
   const int H = L - L / 2, units = (H - slab_border(H) + 15) / 16;
   size_t lds = 2 * size_t(kSlabRows) * slab_stride<R>(H) * sizeof(R);
@@ -720,8 +722,8 @@ template <typename R> SlabShape slab_shape(int L, bool x, int workgroups) {
   const bool f64 = sizeof(R) == 8;
   const bool tail = x && f64 && workgroups > 256 && workgroups < 352;
   const bool few = (workgroups < (x ? (f64 ? 256 : 2) : 128) || tail) && s.rounds > (x || f64 ? 1 : 3);
-  const bool brief = x     ? H <= 16
-                     : f64 ? H <= 32 && workgroups >= 12288
+  const bool brief = x     ? H > 4 && H <= 16
+                     : f64 ? (H <= 32 && workgroups >= 12288) || (H > 12 && H <= 16 && workgroups >= 600)
                            : workgroups >= 1536 && H <= (workgroups < 3072 ? 32 : 16);
   s.lds = lds <= 159 * 1024 && !(x && s.rounds > 2) && !few && !brief ? lds : 0;
   return s;

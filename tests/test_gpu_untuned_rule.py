@@ -1,6 +1,7 @@
 """Which transform an untuned plan takes for odd M = n + 1 on axes of at least one slab of
-lines: the dense product, and chirp-z for M = 121 .. 129.  The result equals the path forced
-through the autotuner's cache file bit for bit, and not the other one's."""
+lines: the dense product, and chirp-z for M = 121 .. 129, for M = 241 .. 255 too along y of
+grids less than 6 wide.  The result equals the path forced through the autotuner's cache
+file bit for bit, and not the other one's."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -9,11 +10,13 @@ torch = pytest.importorskip("torch")
 
 @pytest.mark.parametrize("M,default", [(255, 0), (241, 0), (239, 0), (201, 0), (131, 0), (129, 2), (127, 2), (121, 2),
                                        (119, 0), (97, 0)])
-@pytest.mark.parametrize("axis", [0, 1])
-def test_untuned_path_of_whole_slabs(tmp_path, axis, M, default):
+@pytest.mark.parametrize("axis,width", [(0, 4), (1, 6), (1, 5)])
+def test_untuned_path_of_whole_slabs(tmp_path, axis, width, M, default):
     from paper_1212_1397_amd import helmholtz6 as h6
     arch = torch.cuda.get_device_properties(0).gcnArchName
-    n = [4, 4, 4]
+    n = [width, width, 4]
+    if width == 5 and M >= 241:
+        default = 2
     n[axis] = M - 1
     plan = h6.Plan(n, 1.0 / M, 5.0 + 0.1j, "DDDDDD", precision="mixed")
     x = torch.randn(plan.shape, dtype=torch.complex128, device="cuda")
